@@ -82,7 +82,7 @@ extern "C" {
 #define COBALT_CI16  2   /* complex int16 station samples (16-bit mode)                    */
 #define COBALT_CF32  3   /* complex float32 samples (exact test signals)                   */
 
-#define COBALT_X_FP32        0   /* FP32 channelised data, FP32 VALU correlator (plain form) */
+#define COBALT_X_FP32        0   /* FP32 channelised data, FP32 MFMA correlator (plain form)   */
 #define COBALT_X_FP16_SPLIT  1   /* FP16 hi/lo planes, FP16 MFMA (hh+hl+lh), FP32 accumulate */
 #define COBALT_X_INT8        2   /* int8 requantised data, int8 MFMA, int32 accumulate       */
 

@@ -18,6 +18,7 @@ constexpr int kPitchAlign = kKBlock;           // channelised rows padded to who
 constexpr int kMaxMfmaInputs = 160;            // 5 row blocks of 32 (80 stations)
 constexpr int kMaxFp32Inputs = 256;
 constexpr int kFChunk = 256;                  // channel samples per F-stage workgroup
+constexpr int kCUs = 256;                     // compute units of an MI355X (work splits aim to fill them)
 
 enum SampleType { ST_CI8 = 1, ST_CI16 = 2, ST_CF32 = 3 };
 enum XMode { XM_FP32 = 0, XM_FP16_SPLIT = 1, XM_INT8 = 2 };
@@ -57,7 +58,7 @@ struct XArgs {
     const void* chan;        // channelised buffer
     void* vis;               // [SB*C][B][4] complex
     int64_t chan_stride;     // bytes per channel in the channelised buffer
-    int32_t M, S, n_c, pitch, n_chan, n_blocks8, n_kb;
+    int32_t M, S, n_c, pitch, n_chan, n_kb;
     float out_scale;         // FP16-split: 2^-2k
 };
 

@@ -337,7 +337,6 @@ XArgs make_xargs(const Sizes& z, const cobalt_config& cfg, const void* d_chan, v
     a.n_c = (int)z.n_c;
     a.pitch = (int)z.pitch;
     a.n_chan = (int)(z.SB * z.C);
-    a.n_blocks8 = (int)((z.M + 7) / 8);
     a.n_kb = (int)(z.pitch / kKBlock);
     a.out_scale = std::ldexp(1.0f, -2 * cfg.fp16_prescale_log2);
     return a;

@@ -18,8 +18,8 @@
 //   (imaginary part), so it is not multiplied but added from hl at the end (where registers
 //   allow: every diagonal tile of the 152-input grid).
 //   int8: exact int32 sums.
-// Plain FP32 form: complex FMAs on the VALU over halves of 8x8 blocks of inputs, with partial
-// sums over 128 channel samples folded into running totals.
+// Plain FP32 form: the same two contractions on FP32 operands and FP32 MFMAs over 16x16 tiles, with
+// partial sums over 128 channel samples folded into running totals.
 #include <type_traits>
 
 #include "cobalt_internal.h"
@@ -28,6 +28,7 @@ namespace cobalt {
 namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef int intx16 __attribute__((ext_vector_type(16)));
 typedef int intx4 __attribute__((ext_vector_type(4)));
@@ -351,105 +352,264 @@ hipError_t launch_mode(const XArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ plain FP32 form ---
-constexpr int kF32Kc = 16;        // complex samples per LDS chunk
-// Blocked accumulation: products are summed over kF32Fold channel samples into partial sums,
-// which are then added to the running totals.  A single running sum over all N_c samples
-// leaves a relative rounding error of about u sqrt(N_c) / 6 (u = 2^-24; the additions round
-// at the size of the growing sum); partial sums of b samples folded into the totals leave
-// about u (b / sqrt(N_c) + sqrt(N_c / b)) / 6, smallest near b = sqrt(N_c): 7.7 times less
-// at N_c = 3072 and b = 128.
-constexpr int kF32Fold = 128;
-static_assert(kF32Fold % kF32Kc == 0, "a fold spans whole LDS chunks");
+// ------------------------------------------------------------------ LDS ring ---
+// Chunks (one K block in FP32 and FP16-split mode, four in int8 mode; 256 bytes per row) stream
+// global -> LDS through a ring of `depth` stages of `nch` chunks, depth - 1 of them in flight.
+// Only ceil(M/4)*4 rows are kept per chunk; fragment reads of a row block's padding rows fall on
+// whatever follows inside the LDS array, and only reach outputs that are never stored.
+struct XRing {
+    int nch, depth;          // chunks per stage, stages
+    int n_inst, ipw;         // 1 KB transfers per chunk, transfers per wave and (full) stage
+    int chunk_b;             // bytes per chunk
+    int n_chunk;             // chunks of a channel
+};
 
-// One thread per half (4 rows x 8 columns) of an 8x8 block of inputs in the lower triangle;
-// complex FMAs from an LDS-staged chunk of kF32Kc channel samples.  The half-block keeps the
-// partial sums and the running totals in registers at three waves per SIMD; the kernel
-// stays bound by its FMAs (per chunk step a wave issues 128 FMAs against 12 LDS reads).  A
-// workgroup of up to kF32Threads threads covers a whole channel (every input row staged
-// once) up to 190 blocks (152 inputs).
-constexpr int kF32Threads = 512;
-__global__ __launch_bounds__(kF32Threads) void xstage_fp32_kernel(XArgs a) {
-    // [kF32Kc][ls] complex samples, row r of input at r + r/16: across the lanes of a wave the
-    // 16 distinct (row block, half) operands of a read land in distinct bank pairs
-    extern __shared__ float2 zl[];
-    const int tid = threadIdx.x, nthr = blockDim.x;
-    const int nhalf = a.n_blocks8 * (a.n_blocks8 + 1);   // two halves per lower-triangle block
-    const int groups = (nhalf + nthr - 1) / nthr;
-    const int64_t ch = blockIdx.x / groups;
-    const int g = blockIdx.x % groups;
-    const int rows = 8 * a.n_blocks8, ls = rows + rows / 16 + 1;
-    const float2* __restrict__ z = (const float2*)((const char*)a.chan + ch * a.chan_stride);
+// Wait until at most n of this wave's transfers are outstanding (rounded down to the counts
+// built: a smaller count waits longer, never shorter).
+__device__ __forceinline__ void wait_transfers(int n) {
+    if (n >= 32) asm volatile("s_waitcnt vmcnt(32)" ::: "memory");
+    else if (n >= 24) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
+    else if (n >= 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+    else if (n >= 12) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+    else if (n >= 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    else if (n >= 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+    else if (n >= 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+    else if (n >= 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
+    else if (n >= 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+    else if (n >= 1) asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+// Workgroup barrier that leaves the transfers in flight (a __syncthreads() would wait for them);
+// this wave's LDS reads and writes are complete before it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-    // this thread's 8x8 block (A >= Bk) in the lower triangle of block rows, and its half
-    const int hb = g * nthr + tid;
-    const bool active = hb < nhalf;
-    const int blk = hb >> 1, half = hb & 1;
-    int A = 0, Bk = 0;
-    if (active) {
-        A = (int)((sqrtf(8.f * blk + 1.f) - 1.f) * 0.5f);
-        while (A * (A + 1) / 2 > blk) --A;
-        while ((A + 1) * (A + 2) / 2 <= blk) ++A;
-        Bk = blk - A * (A + 1) / 2;
+// Issue stage s into its ring slot.  Every wave issues exactly ipw transfers of a full stage (the
+// last ones repeat the stage's final transfer), so that counted waits hold for every wave; the
+// last, partial stage may issue fewer.
+template <int MODE, int NWV>
+__device__ __forceinline__ void ring_issue(const XArgs& a, const XRing& q, const char* __restrict__ chan, char* lds, int s, int wave,
+                                           int lane) {
+    const int c0 = s * q.nch, nch = min(q.nch, q.n_chunk - c0);
+    char* buf = lds + (s % q.depth) * (q.nch * q.chunk_b);
+    const int rsub = lane >> 4, p = lane & 15;
+    int ck = 0, i = wave;
+    for (int k = 0; k < q.ipw; ++k, i += NWV) {
+        while (i >= q.n_inst) { i -= q.n_inst; ++ck; }
+        if (ck >= nch) {
+            if (nch < q.nch) break;
+            ck = nch - 1;
+            i = q.n_inst - 1;
+        }
+        const int row = 4 * i + rsub, g = p ^ (row & 15);
+        bool ok = row < a.M;
+        const char* src;
+        if constexpr (MODE == XM_FP32) {
+            src = chan + (int64_t)(c0 + ck) * (a.M * 256) + (row * 256 + g * 16);
+        } else if constexpr (MODE == XM_FP16_SPLIT) {
+            src = chan + (int64_t)(c0 + ck) * (2 * a.M * 128) + ((g >> 3) * (a.M * 128) + row * 128 + (g & 7) * 16);
+        } else {
+            const int kb = 4 * (c0 + ck) + (g >> 2);
+            ok = ok && kb < a.n_kb;
+            src = chan + (int64_t)kb * (a.M * 64) + (row * 64 + (g & 3) * 16);
+        }
+        if (ok) __builtin_amdgcn_global_load_lds((const void*)src, (lds_ptr_t)(buf + ck * q.chunk_b + i * 1024), 16, 0, 2);
     }
-    const int ra = 8 * A + 4 * half;               // first row of this half
-    float vr[4][8], vi[4][8];           // partial sums of the current fold
-    float tr[4][8], ti[4][8];           // running totals
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) { vr[i][j] = 0.f; vi[i][j] = 0.f; tr[i][j] = 0.f; ti[i][j] = 0.f; }
+}
 
-    for (int kc0 = 0; kc0 < a.n_c; kc0 += kF32Kc) {
-        if (kc0 % kF32Fold == 0 && kc0 > 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    tr[i][j] += vr[i][j];
-                    ti[i][j] += vi[i][j];
-                    vr[i][j] = 0.f;
-                    vi[i][j] = 0.f;
-                }
+// Host: ring of at most lds_b bytes (minus `slack` bytes that fragment reads may run past the
+// last chunk).  Stages of about 8 KB per wave keep the barriers few; the depth takes the rest.
+XRing make_ring(int mode, const XArgs& a, int waves, int lds_b, int slack, int nch_multiple) {
+    XRing q{};
+    const int kc = mode == XM_INT8 ? 128 : 32;
+    q.n_chunk = (a.n_c + kc - 1) / kc;
+    q.n_inst = (a.M + 3) / 4;
+    q.chunk_b = q.n_inst * 1024;
+    const int room = (lds_b - slack) / q.chunk_b;                  // chunks that fit
+    int nch = room / 3;                                            // three stages or more
+    nch = nch / nch_multiple * nch_multiple;
+    nch = nch < 1 ? (room >= 2 * nch_multiple ? nch_multiple : 1) : nch > 8 ? 8 : nch;
+    while (nch > nch_multiple && nch * q.n_inst > 8 * waves) nch -= nch_multiple;
+    q.nch = nch;
+    q.ipw = (nch * q.n_inst + waves - 1) / waves;
+    q.depth = room / nch;
+    while (q.depth > 3 && (q.depth - 2) * q.ipw > 32) --q.depth;  // counted waits are built up to 32
+    if (q.depth > 8) q.depth = 8;
+    return q;
+}
+
+// Zero columns >= n_c of the last chunk (`cols` of them from its column `first`) for rows < M.
+template <int MODE>
+__device__ __forceinline__ void zero_columns(const XArgs& a, char* buf, int first, int cols, int tid, int nthr) {
+    for (int id = tid; id < a.M * cols; id += nthr) {
+        const int row = id / cols, c = first + id % cols;
+        if constexpr (MODE == XM_FP32) {
+            *(uint2*)(buf + lds_off(row, c >> 1) + (c & 1) * 8) = make_uint2(0u, 0u);
+        } else if constexpr (MODE == XM_FP16_SPLIT) {
+            *(unsigned*)(buf + lds_off(row, c >> 2) + (c & 3) * 4) = 0u;        // hi
+            *(unsigned*)(buf + lds_off(row, 8 + (c >> 2)) + (c & 3) * 4) = 0u;  // lo
+        } else {
+            *(unsigned short*)(buf + lds_off(row, c >> 3) + (c & 7) * 2) = 0;
         }
-        __syncthreads();
-        for (int id = tid; id < rows * kF32Kc; id += nthr) {
-            const int row = id / kF32Kc, k = id % kF32Kc, col = kc0 + k;
-            float2 v = make_float2(0.f, 0.f);
-            if (row < a.M && col < a.n_c) v = z[((int64_t)(col / kKBlock) * a.M + row) * kKBlock + (col % kKBlock)];
-            zl[k * ls + row + (row >> 4)] = v;
+    }
+}
+
+// The ring's loop over a channel: body(stage buffer, chunks in the stage, stage index) runs with
+// every chunk of the stage in LDS.
+template <int MODE, int NWV, class F>
+__device__ __forceinline__ void ring_loop(const XArgs& a, const XRing& q, const char* __restrict__ chan, char* lds, int tid, F&& body) {
+    constexpr int kc = MODE == XM_INT8 ? 128 : 32;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int n_stage = (q.n_chunk + q.nch - 1) / q.nch, n_full = q.n_chunk / q.nch;
+    for (int s = 0; s < min(q.depth - 1, n_stage); ++s) ring_issue<MODE, NWV>(a, q, chan, lds, s, wave, lane);
+    for (int s = 0; s < n_stage; ++s) {
+        // stages s + 1 .. s + depth - 2 may still be in flight (counted where all of them are full)
+        wait_transfers(s + q.depth - 2 < n_full ? q.ipw * (q.depth - 2) : 0);
+        lds_barrier();                        // ... for every wave; the slot of stage s - 1 is free
+        if (s + q.depth - 1 < n_stage) ring_issue<MODE, NWV>(a, q, chan, lds, s + q.depth - 1, wave, lane);
+        char* buf = lds + (s % q.depth) * (q.nch * q.chunk_b);
+        const int nch = min(q.nch, q.n_chunk - s * q.nch);
+        if (s == n_stage - 1 && a.n_c % kc != 0) {
+            const int first = a.n_c % kc;
+            zero_columns<MODE>(a, buf + (nch - 1) * q.chunk_b, first, kc - first, tid, 64 * NWV);
+            lds_barrier();
         }
-        __syncthreads();
-        if (active) {
-            for (int k = 0; k < kF32Kc; ++k) {
-                float2 xa[4], xb[8];
+        body(buf, nch);
+    }
+    lds_barrier();                            // every wave is done with the chunks
+}
+
+// ------------------------------------------------------------------ plain FP32 form ---
+// FP32 samples and FP32 products on v_mfma_f32_16x16x4_f32 (one FP32 multiply-add per element, as
+// the vector units do, at twice their rate without packed FP32).  The lower triangle of 16 x 16
+// tiles (re and im accumulators) is dealt out as tile lists: `groups` workgroups per channel,
+// n_tg wave groups in each and TPW tiles per wave; the 8 / n_tg waves of a group split the k-steps
+// among them (8 samples each) and add their sums through LDS at the end, in a fixed order.  A
+// 16-byte fragment of lane i (row i % 16, samples 2 (i / 16) and 2 (i / 16) + 1 of a k-step) is
+// four k values of an A and of a B operand; Im takes (-im, re) as B.
+// Bound by the FP32 matrix pipes (a library product reaches 154 TFLOP/s here).  Tiles of 16 waste
+// less of the triangle than tiles of 32 (24 stations: 6 x 256 against 3 x 1024 products per k), and
+// the k-split keeps all eight waves busy at any station count.  Against complex FMAs on the vector
+// units (one thread per 4 x 8 inputs, one workgroup per channel): 60 stations, 512 channels, 3072 samples
+// 1777 -> 1045 us; 8 stations, 64 channels 1472 -> 29 us (that form had one wave per channel).
+// Blocked accumulation: a wave's products over kF32Fold k-steps go into partial sums, which are
+// then added to its running totals.  A single running sum over all N_c samples leaves a relative
+// rounding error of about u sqrt(N_c) / 6 (u = 2^-24; the additions round at the size of the
+// growing sum); partial sums of b samples folded into the totals leave about
+// u (b / sqrt(N_c) + sqrt(N_c / b)) / 6, smallest near b = sqrt(N_c): 7.7 times less at
+// N_c = 3072 and b = 128.
+constexpr int kF32Waves = 8;
+constexpr int kF32LdsB = 147456;
+constexpr int kF32Fold = 16;                  // k-steps of 8 samples
+constexpr int kF32MaxTpw = 9;                 // 144 accumulator registers, two waves per SIMD
+
+struct XF32 {
+    int n_tiles, nb, groups, n_tg;
+};
+
+template <int TPW>
+__global__ __launch_bounds__(64 * kF32Waves, 2) void xstage_f32_kernel(XArgs a, XRing q, XF32 f) {
+    __shared__ __attribute__((aligned(1024))) char lds[kF32LdsB];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t ch = blockIdx.x / f.groups;
+    const int tg = wave % f.n_tg, kpart = wave / f.n_tg, n_kp = kF32Waves / f.n_tg;
+    const char* chan = (const char*)a.chan + ch * a.chan_stride;
+
+    // this wave's tiles: TPW consecutive ones of the column-major lower triangle (tiles past the
+    // end repeat the last one and are not stored)
+    const int t0 = ((int)(blockIdx.x % f.groups) * f.n_tg + tg) * TPW;
+    const int nt = min(TPW, f.n_tiles - t0);  // <= 0: an idle wave (it still moves data)
+    int ti[TPW], tj[TPW];
+    {
+        int J = 0, left = min(t0, f.n_tiles - 1);
+        while (left >= f.nb - J) { left -= f.nb - J; ++J; }
+        int I = J + left;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) xa[i] = zl[k * ls + ra + i + ((ra + i) >> 4)];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) xb[j] = zl[k * ls + 8 * Bk + j + ((8 * Bk + j) >> 4)];
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        vr[i][j] = fmaf(xa[i].x, xb[j].x, fmaf(xa[i].y, xb[j].y, vr[i][j]));
-                        vi[i][j] = fmaf(xa[i].y, xb[j].x, fmaf(-xa[i].x, xb[j].y, vi[i][j]));
-                    }
+        for (int t = 0; t < TPW; ++t) {
+            ti[t] = I;
+            tj[t] = J;
+            if (t + 1 < nt) {
+                if (++I == f.nb) { ++J; I = J; }
             }
         }
     }
-    if (!active) return;
+    floatx4 re[TPW], im[TPW], tre[TPW], tim[TPW];   // partial sums, running totals
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) re[t] = im[t] = tre[t] = tim[t] = floatx4{};
+    int step = kpart, since = 0;              // k-step inside the stage, k-steps since the last fold
+
+    ring_loop<XM_FP32, kF32Waves>(a, q, chan, lds, tid, [&](char* buf, int nch) {
+        if (nt > 0) {
+            for (step = kpart; step < 4 * nch; step += n_kp) {
+                const char* base = buf + (step >> 2) * q.chunk_b + (lane & 15) * kRowB +
+                                   (((4 * (step & 3) + (lane >> 4)) ^ (lane & 15)) << 4);
+#pragma unroll
+                for (int t = 0; t < TPW; ++t) {
+                    const floatx4 A = *(const floatx4*)(base + ti[t] * (16 * kRowB));
+                    const floatx4 B = *(const floatx4*)(base + tj[t] * (16 * kRowB));
+                    re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[0], B[0], re[t], 0, 0, 0);
+                    im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[0], -B[1], im[t], 0, 0, 0);
+                    re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[1], B[1], re[t], 0, 0, 0);
+                    im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[1], B[0], im[t], 0, 0, 0);
+                    re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[2], B[2], re[t], 0, 0, 0);
+                    im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[2], -B[3], im[t], 0, 0, 0);
+                    re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[3], B[3], re[t], 0, 0, 0);
+                    im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[3], B[2], im[t], 0, 0, 0);
+                }
+                if (++since == kF32Fold) {
+                    since = 0;
+#pragma unroll
+                    for (int t = 0; t < TPW; ++t) {
+                        tre[t] += re[t];
+                        tim[t] += im[t];
+                        re[t] = im[t] = floatx4{};
+                    }
+                }
+            }
+        }
+    });
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+        tre[t] += re[t];
+        tim[t] += im[t];
+    }
+    // sums over the k parts, halving their number per round
+    floatx4* red = (floatx4*)lds;             // [k part][wave group][tile][re, im][lane]
+    for (int half = n_kp / 2; half >= 1; half >>= 1) {
+        if (kpart >= half && kpart < 2 * half) {
+            floatx4* dst = red + (size_t)((kpart - half) * f.n_tg + tg) * TPW * 2 * 64 + lane;
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) {
+                dst[(2 * t) * 64] = tre[t];
+                dst[(2 * t + 1) * 64] = tim[t];
+            }
+        }
+        lds_barrier();
+        if (kpart < half) {
+            const floatx4* src = red + (size_t)(kpart * f.n_tg + tg) * TPW * 2 * 64 + lane;
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) {
+                tre[t] += src[(2 * t) * 64];
+                tim[t] += src[(2 * t + 1) * 64];
+            }
+        }
+        lds_barrier();
+    }
+    if (kpart != 0) return;
     const int64_t B = (int64_t)a.S * (a.S + 1) / 2;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int t = 0; t < TPW; ++t) {
+        const int b = 16 * tj[t] + (lane & 15);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int aa = ra + i, b = 8 * Bk + j;
-            if (aa < a.M && b < a.M && (aa >> 1) >= (b >> 1)) {
-                const int s1 = aa >> 1, s2 = b >> 1;
+        for (int r = 0; r < 4; ++r) {
+            const int aa = 16 * ti[t] + 4 * (lane >> 4) + r;
+            const int s1 = aa >> 1, s2 = b >> 1;
+            if (t < nt && aa < a.M && b < a.M && s1 >= s2) {
                 const int64_t idx = (ch * B + (int64_t)s1 * (s1 + 1) / 2 + s2) * 4 + 2 * (aa & 1) + (b & 1);
-                ((float2*)a.vis)[idx] = make_float2(tr[i][j] + vr[i][j], aa == b ? 0.f : ti[i][j] + vi[i][j]);
+                ((float2*)a.vis)[idx] = make_float2(tre[t][r], aa == b ? 0.f : tim[t][r]);
             }
         }
+    }
 }
 
 }  // namespace
@@ -463,11 +623,36 @@ hipError_t launch_xstage_mfma(int x_mode, const XArgs& a, hipStream_t st) {
 
 hipError_t launch_xstage_fp32(const XArgs& a, hipStream_t st) {
     if (a.n_chan <= 0) return hipSuccess;
-    const int nhalf = a.n_blocks8 * (a.n_blocks8 + 1);
-    const int nthr = nhalf < kF32Threads ? (nhalf + 63) / 64 * 64 : kF32Threads;
-    const int groups = (nhalf + nthr - 1) / nthr;
-    const size_t lds = (size_t)kF32Kc * (8 * a.n_blocks8 + (8 * a.n_blocks8) / 16 + 1) * sizeof(float2);
-    hipLaunchKernelGGL(xstage_fp32_kernel, dim3((unsigned)((int64_t)a.n_chan * groups)), dim3(nthr), lds, st, a);
+    XF32 f{};
+    f.nb = (a.M + 15) / 16;
+    f.n_tiles = f.nb * (f.nb + 1) / 2;
+    // Split with the least time per CU: rounds of workgroups x tile slots per channel share.  A
+    // smaller number of workgroups per channel reads the channel fewer times; fewer wave groups
+    // waste fewer slots but need the k-split sums, so ties go to more groups of waves.
+    int best = 0x7fffffff, tpw = 1;
+    for (int groups = 1; groups <= 4; ++groups)
+        for (int n_tg = kF32Waves; n_tg >= 1; n_tg /= 2) {
+            const int per = (f.n_tiles + groups * n_tg - 1) / (groups * n_tg);
+            if (per > kF32MaxTpw) continue;
+            const int64_t rounds = ((int64_t)a.n_chan * groups + kCUs - 1) / kCUs;
+            const int64_t cost = rounds * per * n_tg;
+            if (cost < best) { best = (int)cost; tpw = per; f.groups = groups; f.n_tg = n_tg; }
+        }
+    const int n_kp = kF32Waves / f.n_tg;
+    const XRing q = make_ring(XM_FP32, a, kF32Waves, kF32LdsB, (16 * f.nb - (a.M + 3) / 4 * 4) * kRowB, n_kp == 8 ? 2 : 1);
+    const dim3 grid((unsigned)((int64_t)a.n_chan * f.groups)), block(64 * kF32Waves);
+    switch (tpw) {
+        case 1: hipLaunchKernelGGL(xstage_f32_kernel<1>, grid, block, 0, st, a, q, f); break;
+        case 2: hipLaunchKernelGGL(xstage_f32_kernel<2>, grid, block, 0, st, a, q, f); break;
+        case 3: hipLaunchKernelGGL(xstage_f32_kernel<3>, grid, block, 0, st, a, q, f); break;
+        case 4: hipLaunchKernelGGL(xstage_f32_kernel<4>, grid, block, 0, st, a, q, f); break;
+        case 5: hipLaunchKernelGGL(xstage_f32_kernel<5>, grid, block, 0, st, a, q, f); break;
+        case 6: hipLaunchKernelGGL(xstage_f32_kernel<6>, grid, block, 0, st, a, q, f); break;
+        case 7: hipLaunchKernelGGL(xstage_f32_kernel<7>, grid, block, 0, st, a, q, f); break;
+        case 8: hipLaunchKernelGGL(xstage_f32_kernel<8>, grid, block, 0, st, a, q, f); break;
+        case 9: hipLaunchKernelGGL(xstage_f32_kernel<9>, grid, block, 0, st, a, q, f); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
