@@ -17,7 +17,10 @@ constexpr int kKBlock = 32;                    // channel samples per K block of
 constexpr int kPitchAlign = kKBlock;           // channelised rows padded to whole K blocks
 constexpr int kMaxMfmaInputs = 160;            // 5 row blocks of 32 (80 stations)
 constexpr int kMaxFp32Inputs = 256;
-constexpr int kFChunk = 256;                  // channel samples per F-stage workgroup
+// Per-call host arrays (delays, coarse offsets) travel in the kernel arguments: at most 128
+// stations x 20 bytes, well inside the 4 KB a launch may carry.
+constexpr int kMaxStations = kMaxFp32Inputs / 2;
+constexpr int kFChunk = 256;                  // most channel samples per F-stage workgroup
 constexpr int kCUs = 256;                     // compute units of an MI355X (work splits aim to fill them)
 
 enum SampleType { ST_CI8 = 1, ST_CI16 = 2, ST_CF32 = 3 };
@@ -31,14 +34,15 @@ struct FArgs {
     const float* fir;        // [kT * C]
     const float* bscale;     // [C] bandpass * mode scale (2^k or requant gain)
     const double* f_sb;      // [SB] subband sky centre frequency (Hz)
-    const double* delays;    // [S][2] residual delay (s) at block start / end
-    const int32_t* coarse;   // [S] window start of each station in its rows, or null (0)
     const uint32_t* cflag;   // [S*SB][n_words] flagged channel samples (bit j%32 of word j/32), or null
     int64_t N;               // samples per block window per stream
     int64_t row_len;         // samples per input row (N + guard)
     int32_t C;               // channels: 64 or 256
-    int32_t S, SB, M, n_c, pitch, n_chunks, n_kb, n_words;
+    int32_t S, SB, M, n_c, pitch, n_kb, n_words;
+    int32_t chunk, n_chunks; // channel samples per workgroup (a multiple of 32), workgroups per stream
     double df;               // channel width f_s / C (Hz)
+    double delays[2 * kMaxStations];   // [S][2] residual delay (s) at block start / end
+    int32_t coarse[kMaxStations];      // [S] window start of each station in its rows
 };
 
 // Lost-sample flags -> flagged channel samples (FIR window rule) and the row flags carried
@@ -46,12 +50,12 @@ struct FArgs {
 struct FlagArgs {
     const uint32_t* flags;   // [S][SB][flag_words] lost-sample bits of the input rows, or null
     int64_t flag_words;
-    const int32_t* coarse;   // [S] or null
     const uint32_t* hist_old;// [S*SB] flags of the kHistRows rows before the block, bits 17..31
     uint32_t* hist_new;      // same, for the next block
     uint32_t* cflag;         // [S*SB][n_words]
     int32_t S, SB, n_c, n_words;
     int32_t C;               // samples per row (channels): a multiple of 32
+    int32_t coarse[kMaxStations];      // [S] window start of each station in its rows
 };
 
 struct XArgs {
@@ -95,6 +99,10 @@ hipError_t launch_weights(const uint32_t* cflag, int32_t* weights, int S, int SB
 hipError_t launch_beamformer(const BeamArgs& a, hipStream_t st);
 hipError_t launch_beam_transform(const TfArgs& a, hipStream_t st);
 hipError_t launch_zero_fill(void* p, int64_t bytes, hipStream_t st);
+// Host array -> device through kernel arguments, up to kUploadBytes per launch; `src` is not read
+// after the return.  `dst` 4-byte aligned, `bytes` a multiple of 4.
+constexpr int kUploadBytes = 3968;
+hipError_t launch_upload(void* dst, const void* src, int64_t bytes, hipStream_t st);
 hipError_t launch_device_copy(void* dst, const void* src, int64_t bytes, hipStream_t st);
 hipError_t launch_mfma_probe(int x_mode, int64_t iters, int workgroups, float* sink, hipStream_t st);
 hipError_t launch_device_fanout(void* dst0, void* dst1, const void* src, int64_t bytes, hipStream_t st);

@@ -27,7 +27,7 @@ __global__ __launch_bounds__(64) void chanflag_kernel(FlagArgs a) {
     const int64_t sst = blockIdx.x;                       // s * SB + sb
     const int s = (int)(sst / a.SB);
     const uint32_t* __restrict__ fl = a.flags ? a.flags + sst * a.flag_words : nullptr;
-    const int64_t g = a.coarse ? a.coarse[s] : 0;         // window start in the row
+    const int64_t g = a.coarse[s];         // window start in the row
     const int b = (int)(g & 31);
     const uint32_t lowmask = b ? (1u << b) - 1u : 0u;
     uint32_t carry = a.hist_old[sst];

@@ -21,6 +21,8 @@
 //          FMA and reduced with FP64 rint; the reduced phase is rotated in FP32 with the
 //          hardware sin/cos (argument in revolutions).
 //   Store: lanes with equal h write 32 consecutive channel samples of one channel row.
+#include <cstring>
+
 #include "cobalt_internal.h"
 
 namespace cobalt {
@@ -28,7 +30,6 @@ namespace {
 
 constexpr int kPass = 32;                 // channel samples per pass (= one K block)
 static_assert(kPass == kKBlock, "a pass writes exactly one K block per channel");
-constexpr int kChunk = kFChunk;           // channel samples per workgroup (8 passes)
 constexpr int kRowF2 = 68;                // complex staging row (float2): two 32-point halves, 16 B apart
 constexpr int kHalfF2 = 34;
 constexpr int kRowF1 = 72;                // split staging row (floats): conflict-free 16-byte column reads
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(C) __attribute__((amdgpu_waves_per_eu(fstage_waves<
     const int s = row_in >> 1;
     // wave-uniform bases; per-lane offsets below stay within 2^31 bytes
     // block window of this stream: its row, shifted by the station's coarse delay
-    const raw_t* __restrict__ in = (const raw_t*)a.in + st * a.row_len + (a.coarse ? a.coarse[s] : 0);
+    const raw_t* __restrict__ in = (const raw_t*)a.in + st * a.row_len + a.coarse[s];
     // flagged channel samples of this station and subband (one bit per channel sample)
     const uint32_t* __restrict__ cflag = a.cflag ? a.cflag + ((int64_t)s * a.SB + sb) * a.n_words : nullptr;
     const raw_t* __restrict__ hold = (const raw_t*)a.hist_old + st * kHistC;
@@ -277,8 +278,8 @@ __global__ __launch_bounds__(C) __attribute__((amdgpu_waves_per_eu(fstage_waves<
     const double fsb = a.f_sb[sb];
     const int jj = lane >> 1, hh = lane & 1;
 
-    const int j0 = chunk * kChunk;
-    const int jend = min(j0 + kChunk, a.pitch);
+    const int j0 = chunk * a.chunk;
+    const int jend = min(j0 + a.chunk, a.pitch);
 
     raw_t tail[kHistRows];                     // raw samples of the 15 rows before the pass
     if (j0 >= kHistRows && j0 <= a.n_c) {
@@ -510,6 +511,17 @@ __global__ void zero_fill_kernel(uint4* p, int64_t n16, uint8_t* tail, int64_t n
         for (int64_t i = threadIdx.x; i < ntail; i += blockDim.x) tail[i] = 0;
 }
 
+// A small host table carried in the kernel arguments (a pageable host-to-device copy costs the host
+// a staging copy and the device a copy dispatch of ~3.7 us per array).
+struct UploadArgs {
+    uint32_t data[kUploadBytes / 4];
+    uint32_t* dst;
+    int32_t n;
+};
+__global__ void upload_kernel(UploadArgs a) {
+    for (int i = threadIdx.x; i < a.n; i += 256) a.dst[i] = a.data[i];
+}
+
 template <int ST, int C>
 hipError_t launch_st(int x_mode, const FArgs& a, int n_streams, hipStream_t st) {
     const dim3 grid((unsigned)((int64_t)n_streams * a.n_chunks)), block(C);   // = SB * n_chunks * M
@@ -541,6 +553,20 @@ hipError_t launch_fstage(int sample_type, int x_mode, const FArgs& a, int n_stre
         case ST_CF32: return launch_c<ST_CF32>(x_mode, a, n_streams, st);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_upload(void* dst, const void* src, int64_t bytes, hipStream_t st) {
+    for (int64_t at = 0; at < bytes; at += kUploadBytes) {
+        UploadArgs a;
+        const int64_t n = bytes - at < kUploadBytes ? bytes - at : kUploadBytes;
+        std::memcpy(a.data, (const char*)src + at, (size_t)n);
+        a.dst = (uint32_t*)((char*)dst + at);
+        a.n = (int32_t)(n / 4);
+        hipLaunchKernelGGL(upload_kernel, dim3(1), dim3(256), 0, st, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_zero_fill(void* p, int64_t bytes, hipStream_t st) {

@@ -35,13 +35,11 @@ int fail(int code, const char* fmt, ...) {
     return code;
 }
 
-constexpr int kRing = 8;   // delay staging slots (pinned host + device)
-
 struct Sizes {
     int64_t S, P, SB, C, T, N, n_c, pitch, M, B, streams;
     int64_t sample_bytes, input_bytes, chan_elem_bytes, chan_planes, chan_stride, chan_bytes, vis_bytes;
     int64_t hist_bytes, table_bytes, workspace_bytes;
-    int64_t n_words, cflag_bytes, rowhist_bytes, stage_bytes;
+    int64_t n_words, cflag_bytes, rowhist_bytes;
 };
 
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
@@ -148,9 +146,7 @@ int validate(const cobalt_config* c, Sizes* z) {
     s.chan_bytes = s.SB * s.C * s.chan_stride;
     s.vis_bytes = s.SB * s.C * s.B * 4 * 8;
     s.hist_bytes = s.streams * kHistRows * s.C * s.sample_bytes;
-    s.stage_bytes = round_up(s.S * 16 + s.S * 4, 256);         // per ring slot: delays [S][2], offsets [S]
-    s.table_bytes = round_up(kT * s.C * 4, 256) + round_up(s.C * 4, 256) + round_up(s.SB * 8, 256) +
-                    kRing * s.stage_bytes;
+    s.table_bytes = round_up(kT * s.C * 4, 256) + round_up(s.C * 4, 256) + round_up(s.SB * 8, 256);
     s.n_words = s.pitch / 32;
     s.cflag_bytes = s.S * s.SB * s.n_words * 4;
     s.rowhist_bytes = s.S * s.SB * 4;
@@ -178,11 +174,6 @@ struct cobalt_plan {
     float* d_fir = nullptr;
     float* d_bscale = nullptr;
     double* d_fsb = nullptr;
-    char* d_stage[kRing] = {};   // per slot: delays [S][2] float64, coarse offsets [S] int32
-    char* h_stage = nullptr;     // pinned [kRing][stage_bytes]
-    hipEvent_t ring_ev[kRing] = {};
-    bool ring_used[kRing] = {};
-    int ring_next = 0;
     hipEvent_t done_ev = nullptr;
     hipStream_t last_stream = nullptr;
     bool has_last = false;
@@ -210,10 +201,7 @@ int hip_fail(hipError_t e, const char* what) {
 
 void free_plan(cobalt_plan* p) {
     if (!p) return;
-    for (int i = 0; i < kRing; ++i)
-        if (p->ring_ev[i]) (void)hipEventDestroy(p->ring_ev[i]);
     if (p->done_ev) (void)hipEventDestroy(p->done_ev);
-    if (p->h_stage) (void)hipHostFree(p->h_stage);
     if (p->d_ws && p->owns_ws) (void)hipFree(p->d_ws);
     delete p;
 }
@@ -235,43 +223,22 @@ int end_call(cobalt_plan* p, hipStream_t st) {
     return COBALT_OK;
 }
 
-// Copy the caller's delays into a ring slot (pinned host -> device) on stream st.
-// Per-call host arrays (residual delays, coarse offsets) go through a pinned ring of kRing
-// slots, each guarded by the event of its last copy, so the caller may reuse its arrays at
-// once and the copy stays ordered on the call's stream.
-int stage_block(cobalt_plan* p, const double* h_delays, const int32_t* h_coarse, int64_t max_offset, hipStream_t st,
-                const double** d_delays, const int32_t** d_coarse) {
-    const int S = (int)p->z.S;
-    for (int i = 0; i < 2 * S; ++i)
+// Validity of the per-call host arrays.  They travel in the kernel arguments, so the caller may
+// reuse them as soon as the call returns.
+int check_block(const Sizes& z, const double* h_delays, const int32_t* h_coarse, int64_t max_offset) {
+    for (int i = 0; i < 2 * z.S; ++i)
         if (!std::isfinite(h_delays[i])) return fail(COBALT_EINVAL, "h_delays[%d] is not finite", i);
     if (h_coarse)
-        for (int i = 0; i < S; ++i)
+        for (int i = 0; i < z.S; ++i)
             if (h_coarse[i] < 0 || h_coarse[i] > max_offset)
                 return fail(COBALT_EINVAL, "coarse offset of station %d is %d; must lie in 0..%lld", i, h_coarse[i],
                             (long long)max_offset);
-    const int slot = p->ring_next;
-    p->ring_next = (p->ring_next + 1) % kRing;
-    if (p->ring_used[slot]) {
-        hipError_t e = hipEventSynchronize(p->ring_ev[slot]);   // the slot's previous copy has run
-        if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize");
-    }
-    char* h = p->h_stage + (size_t)slot * p->z.stage_bytes;
-    std::memcpy(h, h_delays, sizeof(double) * 2 * S);
-    const size_t bytes = sizeof(double) * 2 * S + (h_coarse ? sizeof(int32_t) * S : 0);
-    if (h_coarse) std::memcpy(h + sizeof(double) * 2 * S, h_coarse, sizeof(int32_t) * S);
-    hipError_t e = hipMemcpyAsync(p->d_stage[slot], h, bytes, hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(delays)");
-    e = hipEventRecord(p->ring_ev[slot], st);
-    if (e != hipSuccess) return hip_fail(e, "hipEventRecord(delays)");
-    p->ring_used[slot] = true;
-    *d_delays = (const double*)p->d_stage[slot];
-    *d_coarse = h_coarse ? (const int32_t*)(p->d_stage[slot] + sizeof(double) * 2 * S) : nullptr;
     return COBALT_OK;
 }
 
 // Flagged channel samples of this block (null when nothing can be flagged: no flags given
 // and the carried row flags are known to be clear).
-int run_flags(cobalt_plan* p, const uint32_t* d_flags, int64_t row_len, const int32_t* d_coarse, hipStream_t st,
+int run_flags(cobalt_plan* p, const uint32_t* d_flags, int64_t row_len, const int32_t* h_coarse, hipStream_t st,
               const uint32_t** cflag) {
     const Sizes& z = p->z;
     *cflag = nullptr;
@@ -279,7 +246,7 @@ int run_flags(cobalt_plan* p, const uint32_t* d_flags, int64_t row_len, const in
     FlagArgs a{};
     a.flags = d_flags;
     a.flag_words = (row_len + 31) / 32;
-    a.coarse = d_coarse;
+    if (h_coarse) std::memcpy(a.coarse, h_coarse, sizeof(int32_t) * z.S);
     a.hist_old = p->d_rowhist[p->rowhist_cur];
     a.hist_new = p->d_rowhist[p->rowhist_cur ^ 1];
     a.cflag = p->d_cflag;
@@ -299,8 +266,8 @@ int run_flags(cobalt_plan* p, const uint32_t* d_flags, int64_t row_len, const in
 }
 
 FArgs make_fargs(const Sizes& z, const cobalt_config& cfg, const void* d_in, int64_t row_len, const void* hist_old,
-                 void* hist_new, const float* fir, const float* bscale, const double* fsb, const double* d_delays,
-                 const int32_t* d_coarse, const uint32_t* cflag, void* d_chan) {
+                 void* hist_new, const float* fir, const float* bscale, const double* fsb, const double* h_delays,
+                 const int32_t* h_coarse, const uint32_t* cflag, void* d_chan) {
     FArgs a{};
     a.in = d_in;
     a.hist_old = hist_old;
@@ -309,8 +276,8 @@ FArgs make_fargs(const Sizes& z, const cobalt_config& cfg, const void* d_in, int
     a.fir = fir;
     a.bscale = bscale;
     a.f_sb = fsb;
-    a.delays = d_delays;
-    a.coarse = d_coarse;
+    std::memcpy(a.delays, h_delays, sizeof(double) * 2 * z.S);
+    if (h_coarse) std::memcpy(a.coarse, h_coarse, sizeof(int32_t) * z.S);
     a.cflag = cflag;
     a.N = z.N;
     a.row_len = row_len;
@@ -320,7 +287,8 @@ FArgs make_fargs(const Sizes& z, const cobalt_config& cfg, const void* d_in, int
     a.M = (int)z.M;
     a.n_c = (int)z.n_c;
     a.pitch = (int)z.pitch;
-    a.n_chunks = (int)((z.pitch + kFChunk - 1) / kFChunk);
+    a.chunk = kFChunk;
+    a.n_chunks = (int)((z.pitch + a.chunk - 1) / a.chunk);
     a.n_kb = (int)(z.pitch / kKBlock);
     a.df = cfg.sample_rate_hz / (double)z.C;
     a.C = (int)z.C;
@@ -348,12 +316,12 @@ int launch_x(const cobalt_config& cfg, const XArgs& a, hipStream_t st) {
     return COBALT_OK;
 }
 
-int run_fstage(cobalt_plan* p, const void* d_in, int64_t row_len, const double* d_delays, const int32_t* d_coarse,
+int run_fstage(cobalt_plan* p, const void* d_in, int64_t row_len, const double* h_delays, const int32_t* h_coarse,
                const uint32_t* cflag, void* d_chan, hipStream_t st) {
     const Sizes& z = p->z;
     if (z.n_c == 0) return COBALT_OK;       // empty block: nothing to filter, history unchanged
     const FArgs a = make_fargs(z, p->cfg, d_in, row_len, p->d_hist[p->hist_cur], p->d_hist[p->hist_cur ^ 1], p->d_fir,
-                               p->d_bscale, p->d_fsb, d_delays, d_coarse, cflag, d_chan);
+                               p->d_bscale, p->d_fsb, h_delays, h_coarse, cflag, d_chan);
     hipError_t e = launch_fstage(p->cfg.sample_type, p->cfg.x_mode, a, (int)z.streams, st);
     if (e != hipSuccess) return hip_fail(e, "F-stage launch");
     p->hist_cur ^= 1;
@@ -449,14 +417,7 @@ int cobalt::plan_create_impl(const cobalt_config* cfg, void* d_workspace, cobalt
     p->d_fir = (float*)q;         q += round_up(kT * z.C * 4, 256);
     p->d_bscale = (float*)q;      q += round_up(z.C * 4, 256);
     p->d_fsb = (double*)q;        q += round_up(z.SB * 8, 256);
-    for (int i = 0; i < kRing; ++i) { p->d_stage[i] = q; q += z.stage_bytes; }
 
-    e = hipHostMalloc((void**)&p->h_stage, (size_t)z.stage_bytes * kRing, hipHostMallocDefault);
-    if (e != hipSuccess) { free_plan(p); (void)hipGetLastError(); return fail(COBALT_ENOMEM, "hipHostMalloc failed"); }
-    for (int i = 0; i < kRing; ++i) {
-        e = hipEventCreateWithFlags(&p->ring_ev[i], hipEventDisableTiming);
-        if (e != hipSuccess) { free_plan(p); return hip_fail(e, "hipEventCreate"); }
-    }
     e = hipEventCreateWithFlags(&p->done_ev, hipEventDisableTiming);
     if (e != hipSuccess) { free_plan(p); return hip_fail(e, "hipEventCreate"); }
 
@@ -533,17 +494,15 @@ static int do_fx(cobalt_plan* p, const void* d_in, const double* h_delays, const
     DeviceGuard dg(p->device);
     if (!dg.ok) return fail(COBALT_EDEVICE, "cannot select the plan's device");
     hipStream_t st = (hipStream_t)stream;
-    int rc = begin_call(p, st);
+    int rc = check_block(z, h_delays, h_coarse, row_len - z.N);
     if (rc) return rc;
-    const double* d_delays = nullptr;
-    const int32_t* d_coarse = nullptr;
-    rc = stage_block(p, h_delays, h_coarse, row_len - z.N, st, &d_delays, &d_coarse);
+    rc = begin_call(p, st);
     if (rc) return rc;
     const uint32_t* cflag = nullptr;
-    rc = run_flags(p, d_flags, row_len, d_coarse, st, &cflag);
+    rc = run_flags(p, d_flags, row_len, h_coarse, st, &cflag);
     if (rc) return rc;
     void* chan = d_chan ? d_chan : p->d_chan;
-    rc = run_fstage(p, d_in, row_len, d_delays, d_coarse, cflag, chan, st);
+    rc = run_fstage(p, d_in, row_len, h_delays, h_coarse, cflag, chan, st);
     if (rc) return rc;
     if (d_weights) {
         hipError_t e = launch_weights(cflag, d_weights, (int)z.S, (int)z.SB, (int)z.n_c, (int)z.n_words, st);
@@ -639,16 +598,14 @@ int cobalt_beamform(cobalt_plan* p, const void* d_in, const double* h_delays, co
     DeviceGuard dg(p->device);
     if (!dg.ok) return fail(COBALT_EDEVICE, "cannot select the plan's device");
     hipStream_t st = (hipStream_t)stream;
-    rc = begin_call(p, st);
+    rc = check_block(p->z, h_delays, nullptr, 0);
     if (rc) return rc;
-    const double* d_delays = nullptr;
-    const int32_t* d_coarse = nullptr;
-    rc = stage_block(p, h_delays, nullptr, 0, st, &d_delays, &d_coarse);
+    rc = begin_call(p, st);
     if (rc) return rc;
     const uint32_t* cflag = nullptr;
     rc = run_flags(p, nullptr, p->z.N, nullptr, st, &cflag);
     if (rc) return rc;
-    rc = run_fstage(p, d_in, p->z.N, d_delays, nullptr, cflag, p->d_chan, st);
+    rc = run_fstage(p, d_in, p->z.N, h_delays, nullptr, cflag, p->d_chan, st);
     if (rc) return rc;
     rc = run_beam(p, p->d_chan, bp, d_coherent, d_voltages, d_incoherent, st);
     if (rc) return rc;
@@ -850,10 +807,10 @@ int cobalt_correlate_noalloc(const cobalt_config* cfg, const void* d_in, const d
         return fail(COBALT_EINVAL, "device pointers must be 16-byte aligned");
     if (d_hist_in && d_hist_in == d_hist_out)
         return fail(COBALT_EINVAL, "d_hist_in and d_hist_out must differ (the F stage reads one while writing the other)");
-    for (int i = 0; i < 2 * z.S; ++i)
-        if (!std::isfinite(h_delays[i])) return fail(COBALT_EINVAL, "h_delays[%d] is not finite", i);
+    rc = check_block(z, h_delays, nullptr, 0);
+    if (rc != COBALT_OK) return rc;
     // scratch layout: channelised block | zero history | discarded history | FIR | bandpass x scale |
-    // subband frequencies | delays
+    // subband frequencies
     const int64_t hist = round_up(z.hist_bytes, 256);
     const int64_t o_chan = 0;
     const int64_t o_hzero = o_chan + round_up(z.chan_bytes, 256);
@@ -861,8 +818,7 @@ int cobalt_correlate_noalloc(const cobalt_config* cfg, const void* d_in, const d
     const int64_t o_fir = o_hdrop + (d_hist_out ? 0 : hist);
     const int64_t o_bsc = o_fir + round_up(kT * z.C * 4, 256);
     const int64_t o_fsb = o_bsc + round_up(z.C * 4, 256);
-    const int64_t o_del = o_fsb + round_up(z.SB * 8, 256);
-    const int64_t total = o_del + round_up(z.S * 16, 256);
+    const int64_t total = o_fsb + round_up(z.SB * 8, 256);
     if (total > (int64_t)kScratchBytes)
         return fail(COBALT_EUNSUPPORTED,
                     "this setting needs %lld bytes of scratch; the no-allocation entry point has %zu (use a plan)",
@@ -876,11 +832,11 @@ int cobalt_correlate_noalloc(const cobalt_config* cfg, const void* d_in, const d
                               : cfg->x_mode == COBALT_X_INT8   ? (double)cfg->requant_gain
                                                                : 1.0;
     for (int c = 0; c < z.C; ++c) bscale[c] = (float)((cfg->h_bandpass ? (double)cfg->h_bandpass[c] : 1.0) * mode_scale);
-    // host -> scratch copies from pageable memory return once the source has been read
-    hipError_t e = hipMemcpyAsync(base + o_fir, cfg->h_fir, sizeof(float) * kT * z.C, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(base + o_bsc, bscale, sizeof(float) * z.C, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(base + o_fsb, cfg->h_subband_freq_hz, sizeof(double) * z.SB, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(base + o_del, h_delays, sizeof(double) * 2 * z.S, hipMemcpyHostToDevice, st);
+    // the tables travel in kernel arguments: nothing of the caller's is read after the call, also
+    // when the call is captured into a graph
+    hipError_t e = launch_upload(base + o_fir, cfg->h_fir, sizeof(float) * kT * z.C, st);
+    if (e == hipSuccess) e = launch_upload(base + o_bsc, bscale, sizeof(float) * z.C, st);
+    if (e == hipSuccess) e = launch_upload(base + o_fsb, cfg->h_subband_freq_hz, sizeof(double) * z.SB, st);
     if (e != hipSuccess) return hip_fail(e, "table upload");
     if (!d_hist_in) {
         e = launch_zero_fill(base + o_hzero, hist, st);      // a fill kernel, no memset node
@@ -889,7 +845,7 @@ int cobalt_correlate_noalloc(const cobalt_config* cfg, const void* d_in, const d
     const FArgs a = make_fargs(z, *cfg, d_in, z.N, d_hist_in ? d_hist_in : base + o_hzero,
                                d_hist_out ? d_hist_out : base + o_hdrop, (const float*)(base + o_fir),
                                (const float*)(base + o_bsc), (const double*)(base + o_fsb),
-                               (const double*)(base + o_del), nullptr, nullptr, base + o_chan);
+                               h_delays, nullptr, nullptr, base + o_chan);
     e = launch_fstage(cfg->sample_type, cfg->x_mode, a, (int)z.streams, st);
     if (e != hipSuccess) return hip_fail(e, "F-stage launch");
     return launch_x(*cfg, make_xargs(z, *cfg, base + o_chan, d_vis), st);
