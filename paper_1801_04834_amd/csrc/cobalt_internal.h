@@ -20,7 +20,6 @@ constexpr int kMaxFp32Inputs = 256;
 // Per-call host arrays (delays, coarse offsets) travel in the kernel arguments: at most 128
 // stations x 20 bytes, well inside the 4 KB a launch may carry.
 constexpr int kMaxStations = kMaxFp32Inputs / 2;
-constexpr int kFChunk = 256;                  // most channel samples per F-stage workgroup
 constexpr int kCUs = 256;                     // compute units of an MI355X (work splits aim to fill them)
 
 enum SampleType { ST_CI8 = 1, ST_CI16 = 2, ST_CF32 = 3 };

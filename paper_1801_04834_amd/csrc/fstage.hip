@@ -10,8 +10,8 @@
 // is formed in double precision; the rotation runs in single precision (sec. 7.5, sec. 8).
 //
 // Work decomposition (one wave64 per workgroup):
-//   workgroup = one input stream (station, polarisation, subband) x one chunk of 256
-//   channel samples, processed in passes of 32 channel samples.
+//   workgroup = one input stream (station, polarisation, subband) x one chunk of 32 to 256
+//   channel samples (the launch's choice), processed in passes of 32 channel samples.
 //   FIR:   lane p is FIR phase p; it keeps a 15-row sliding window in registers, so every
 //          input sample is read from HBM once (coalesced 64-lane rows).
 //   FFT:   the first radix-2 decimation-in-frequency stage runs across lanes p and p+32

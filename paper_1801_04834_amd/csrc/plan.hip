@@ -265,6 +265,25 @@ int run_flags(cobalt_plan* p, const uint32_t* d_flags, int64_t row_len, const in
     return COBALT_OK;
 }
 
+// Channel samples per F-stage workgroup.  Each workgroup reads 15 rows of overlap and sets up its
+// taps and twiddles once, so long chunks do less work (and draw less power, which sets the clock of
+// a large block); short ones fill the chip when there are few streams and leave a shorter last
+// round.  Measured, us at chunks of 256 / 128 / 64 / 32 (whole blocks F + X, then the F stage alone):
+//   64 channels, 16-bit:  76 st x 64 SB 8818 / 8903 / 8901 / 9059;  76 x 16  2203 / 2202 / 2217 / 2252;
+//                         24 x 32  1372 / 1357 / 1344 / 1349;  37 x 11 ragged  435 / 427 / 425 / 436;
+//                         F alone: 40 x 4  181 / 158 / 158 / 153;  8 x 2, 512 samples  46 / 27 / 18 / 13
+//   64 channels, 8-bit:   76 x 128  9675 / 9720 / 10240 / 10120;  F alone: 20 x 4  79 / 73 / 74 / 72
+//   256 channels, 16-bit, F alone: 48 x 61  3261 / 3313 / 3308 / 3459;  24 x 8  243 / 228 / 230 / 242;
+//                         13 x 5, 300 samples  80 / 56 / 46 / 44
+// (8-bit samples are bound by the vector units, which the overlap loads most.)
+int fstage_chunk(int sample_type, int64_t C, int64_t streams, int64_t pitch) {
+    const auto groups = [&](int64_t chunk) { return streams * ((pitch + chunk - 1) / chunk); };
+    if (C == 256) return groups(256) >= 8192 ? 256 : groups(128) >= 2048 ? 128 : 32;
+    if (groups(256) >= 24576) return 256;
+    const int mid = sample_type == COBALT_CI8 ? 128 : 64;
+    return groups(mid) >= 16384 ? mid : 32;
+}
+
 FArgs make_fargs(const Sizes& z, const cobalt_config& cfg, const void* d_in, int64_t row_len, const void* hist_old,
                  void* hist_new, const float* fir, const float* bscale, const double* fsb, const double* h_delays,
                  const int32_t* h_coarse, const uint32_t* cflag, void* d_chan) {
@@ -287,7 +306,7 @@ FArgs make_fargs(const Sizes& z, const cobalt_config& cfg, const void* d_in, int
     a.M = (int)z.M;
     a.n_c = (int)z.n_c;
     a.pitch = (int)z.pitch;
-    a.chunk = kFChunk;
+    a.chunk = fstage_chunk(cfg.sample_type, z.C, z.streams, z.pitch);
     a.n_chunks = (int)((z.pitch + a.chunk - 1) / a.chunk);
     a.n_kb = (int)(z.pitch / kKBlock);
     a.df = cfg.sample_rate_hz / (double)z.C;
