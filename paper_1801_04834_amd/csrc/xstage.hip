@@ -6,17 +6,18 @@
 // contractions over K = 2 N_c interleaved (re, im) values:
 //     Re V[a][b] = sum_k A[a][k] A[b][k]         (A = interleaved rows of Z)
 //     Im V[a][b] = sum_k A[a][k] A'[b][k]        (A' = per sample (re, im) -> (-im, re))
-// One workgroup owns one channel and keeps every lower-triangle 32x32 tile of V in
-// accumulators; channel rows stream through LDS once.  An MFMA fragment of row block I
-// (lane i: row 32I + i%32, 8 halves / 16 bytes of K) is simultaneously an A operand (row
-// I) and a B operand (column I), so both operands of a tile come from the same LDS reads
-// and the k order inside a fragment never matters.  A' is built in registers from the
-// B-role fragments.
+// One workgroup owns one channel and keeps every lower-triangle 16x16 tile of V in accumulators;
+// channel rows stream through LDS once.  An MFMA fragment of row block I (lane i: row 16I + i%16,
+// 16 bytes of K) is simultaneously an A operand (row I) and a B operand (column I), so both
+// operands of a tile come from the same LDS reads and the k order inside a fragment never matters.
+// A' is built in registers from the B-role fragments.
 //   FP16-split: Z*2^k = hi + lo (two fp16 planes); V ~= hh + hl + lh accumulated in FP32
-//   (the dropped lo*lo term is below 2^-22 of |Z|^2), scaled back by 2^-2k.  On a diagonal
-//   tile (I = J) the lh product is the transpose of hl (real part) and minus its transpose
-//   (imaginary part), so it is not multiplied but added from hl at the end (where registers
-//   allow: every diagonal tile of the 152-input grid).
+//   (the dropped lo*lo term is below 2^-22 of |Z|^2), scaled back by 2^-2k.  A diagonal tile (I = J)
+//   needs h h^T + h l^T + l h^T: it accumulates W = h (h + 2 l)^T in two products (2 l is exact) and
+//   takes (W + W^T) / 2 (real part) or (W - W^T) / 2 (imaginary part) at the end.  Where a wave sums
+//   all k-steps itself, h l^T has accumulators of its own: the MFMAs round towards zero, and the long
+//   sums of the autos would otherwise be rounded twice per k-step (relative error against 64 bits at
+//   76 stations 7.3e-7 instead of 4.7e-7).
 //   int8: exact int32 sums.
 // Plain FP32 form: the same two contractions on FP32 operands and FP32 MFMAs over 16x16 tiles, with
 // partial sums over 128 channel samples folded into running totals.
@@ -29,8 +30,6 @@ namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef int intx16 __attribute__((ext_vector_type(16)));
 typedef int intx4 __attribute__((ext_vector_type(4)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
@@ -56,39 +55,6 @@ constexpr int tile_I(int R, int idx) {
     while (idx >= R - J) { idx -= R - J; ++J; }
     return J + idx;
 }
-constexpr int kTilesPerWave = 4;
-// blocks used by wave W as A (row) or B (column) operands
-constexpr unsigned wave_blocks(int R, int W, bool as_b) {
-    unsigned m = 0;
-    for (int t = kTilesPerWave * W; t < kTilesPerWave * W + kTilesPerWave && t < tile_count(R); ++t)
-        m |= 1u << (as_b ? tile_J(R, t) : tile_I(R, t));
-    return m;
-}
-
-// Whether wave W of an R-block grid forms lh of its diagonal tiles from hl (FP16-split): each
-// such tile holds one more accumulator pair, so only where at most 5 pairs fit in registers.
-constexpr bool diag_from_hl(int R, int W) {
-    int n = 0, d = 0;
-    for (int t = kTilesPerWave * W; t < kTilesPerWave * W + kTilesPerWave && t < tile_count(R); ++t) {
-        ++n;
-        if (tile_I(R, t) == tile_J(R, t)) ++d;
-    }
-    return n + d <= 5;
-}
-
-template <int MODE> struct XCfg;
-template <> struct XCfg<XM_FP16_SPLIT> {
-    static constexpr int kKc = 32;            // complex samples per chunk (one K block)
-    static constexpr int kSteps = 4;          // k-steps of 16 halves per chunk
-    using acc_t = floatx16;
-    using frag_t = half8;
-};
-template <> struct XCfg<XM_INT8> {
-    static constexpr int kKc = 128;           // complex samples per chunk (four K blocks)
-    static constexpr int kSteps = 8;          // k-steps of 32 bytes per chunk
-    using acc_t = intx16;
-    using frag_t = intx4;
-};
 constexpr int kRowB = 256;                    // LDS bytes per row and chunk (16 granules of 16 B)
 
 // LDS rows are XOR-swizzled in 16-byte granules (granule g of row r is stored at g ^ (r%16)),
@@ -115,242 +81,6 @@ __device__ __forceinline__ uintx4 swapneg_i8(uintx4 d) {
 }
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
-
-// Issue the global -> LDS transfers of one chunk (rows < M) into LDS buffer `buf`.  One
-// instruction moves 64 lanes x 16 B into 1 KB of consecutive LDS (4 rows); lane L of
-// instruction i fills row 4i + L/16, stored granule L%16.  Rows >= M are never written.
-//   FP16-split chunk = K block kb: [hi: M rows x 128 B][lo: M rows x 128 B]; logical granule
-//   g < 8 is hi bytes 16g.., g >= 8 lo bytes 16(g-8)...
-//   int8 chunk = K blocks kb..kb+3, each [M rows x 64 B]; logical granule g is block g/4,
-//   bytes 16(g%4)...  Blocks past the last one are not loaded.
-template <int MODE>
-__device__ __forceinline__ void issue_chunk(const XArgs& a, const char* __restrict__ chan, char* buf, int kc0, int wave, int lane) {
-    const int n_inst = (a.M + 3) / 4;
-    const int rsub = lane >> 4, p = lane & 15;
-    for (int i = wave; i < n_inst; i += 4) {
-        const int row = 4 * i + rsub;
-        const int g = p ^ (row & 15);
-        const char* src;
-        bool ok = row < a.M;
-        if constexpr (MODE == XM_FP16_SPLIT) {
-            const char* blk = chan + (int64_t)(kc0 / kKBlock) * (2 * a.M * 128);
-            src = blk + (g >> 3) * (a.M * 128) + row * 128 + (g & 7) * 16;
-        } else {
-            const int kb = kc0 / kKBlock + (g >> 2);
-            ok = ok && kb < a.n_kb;
-            src = chan + (int64_t)kb * (a.M * 64) + row * 64 + (g & 3) * 16;
-        }
-        // non-temporal: each byte of the channelised data is read once (measured ~1.5 % faster)
-        if (ok) __builtin_amdgcn_global_load_lds((const void*)src, (lds_ptr_t)(buf + i * 1024), 16, 0, 2);
-    }
-}
-
-// Zero the LDS entries of columns >= N_c (the last, partial chunk) and of K blocks that were
-// not loaded, for rows < M.
-template <int MODE>
-__device__ __forceinline__ void zero_tail(const XArgs& a, char* buf, int kc0, int tid) {
-    constexpr int kKc = XCfg<MODE>::kKc;
-    const int first = a.n_c - kc0;                     // first column to clear
-    const int cols = kKc - first;
-    for (int id = tid; id < a.M * cols; id += 256) {
-        const int row = id / cols, c = first + id % cols;
-        if constexpr (MODE == XM_FP16_SPLIT) {
-            *(unsigned*)(buf + lds_off(row, c >> 2) + (c & 3) * 4) = 0u;        // hi
-            *(unsigned*)(buf + lds_off(row, 8 + (c >> 2)) + (c & 3) * 4) = 0u;  // lo
-        } else {
-            *(unsigned short*)(buf + lds_off(row, c >> 3) + (c & 7) * 2) = 0;
-        }
-    }
-}
-
-template <int MODE, int R, int W>
-__device__ __forceinline__ void xwave(const XArgs& a, const char* __restrict__ chan, char* lds, int tid) {
-    using C_ = XCfg<MODE>;
-    using acc_t = typename C_::acc_t;
-    using frag_t = typename C_::frag_t;
-    constexpr int NT = tile_count(R);
-    constexpr int T0 = kTilesPerWave * W;
-    constexpr int NW = NT - T0 <= 0 ? 0 : (NT - T0 > kTilesPerWave ? kTilesPerWave : NT - T0);
-    constexpr unsigned useA = wave_blocks(R, W, false) | wave_blocks(R, W, true);
-    constexpr unsigned useB = wave_blocks(R, W, true);
-    constexpr bool kDiagHl = MODE == XM_FP16_SPLIT && diag_from_hl(R, W);
-    constexpr int kBufB = R * 32 * kRowB;
-    const int lane = tid & 63;
-
-    acc_t vre[kTilesPerWave], vim[kTilesPerWave];
-    acc_t xre[kTilesPerWave], xim[kTilesPerWave];     // hl of diagonal tiles (FP16-split)
-#pragma unroll
-    for (int t = 0; t < kTilesPerWave; ++t) {
-        vre[t] = acc_t{};
-        vim[t] = acc_t{};
-        xre[t] = acc_t{};
-        xim[t] = acc_t{};
-    }
-
-    // rows M .. 32R-1 stay zero in both buffers
-    for (int off = a.M * kRowB + tid * 16; off < kBufB; off += 256 * 16) {
-        *(uint4*)(lds + off) = make_uint4(0, 0, 0, 0);
-        *(uint4*)(lds + kBufB + off) = make_uint4(0, 0, 0, 0);
-    }
-    __syncthreads();
-    if (a.n_c > 0) issue_chunk<MODE>(a, chan, lds, 0, W, lane);
-
-    int cur = 0;
-    for (int kc0 = 0; kc0 < a.n_c; kc0 += C_::kKc) {
-        char* buf = lds + cur * kBufB;
-        __builtin_amdgcn_s_waitcnt(0);        // this wave's transfers of chunk kc0 have landed
-        __syncthreads();                      // ... and everyone's; the other buffer is free
-        if (kc0 + C_::kKc < a.n_c) issue_chunk<MODE>(a, chan, lds + (cur ^ 1) * kBufB, kc0 + C_::kKc, W, lane);
-        if (kc0 + C_::kKc > a.n_c) {          // last, partial chunk (uniform)
-            zero_tail<MODE>(a, buf, kc0, tid);
-            __syncthreads();
-        }
-        if constexpr (NW > 0) {
-#pragma unroll
-            for (int ks = 0; ks < C_::kSteps; ++ks) {
-                const int row = lane & 31;
-                const int g = 2 * ks + (lane >> 5);
-                if constexpr (MODE == XM_FP16_SPLIT) {
-                    uintx4 fh[R], fl[R], gh[R], gl[R];
-                    static_for<R>([&](auto bi) {
-                        constexpr int b = decltype(bi)::value;
-                        if constexpr ((useA >> b) & 1u) {
-                            fh[b] = *(const uintx4*)(buf + lds_off(32 * b + row, g));
-                            fl[b] = *(const uintx4*)(buf + lds_off(32 * b + row, 8 + g));
-                        }
-                        if constexpr ((useB >> b) & 1u) {
-                            gh[b] = swapneg_f16(fh[b]);
-                            gl[b] = swapneg_f16(fl[b]);
-                        }
-                    });
-                    // three products (hh, hl, lh), each over all tiles: independent accumulators
-                    // between dependent MFMAs; diagonal tiles keep hl apart and skip lh
-                    static_for<3>([&](auto pi) {
-                        constexpr int pr = decltype(pi)::value;
-                        static_for<NW>([&](auto ti) {
-                            constexpr int t = decltype(ti)::value;
-                            constexpr int I = tile_I(R, T0 + t), J = tile_J(R, T0 + t);
-                            constexpr bool dg = kDiagHl && I == J;
-                            if constexpr (!(dg && pr == 2)) {
-                                const frag_t A = __builtin_bit_cast(frag_t, pr == 2 ? fl[I] : fh[I]);
-                                const frag_t B = __builtin_bit_cast(frag_t, pr == 1 ? fl[J] : fh[J]);
-                                const frag_t Bs = __builtin_bit_cast(frag_t, pr == 1 ? gl[J] : gh[J]);
-                                if constexpr (dg && pr == 1) {
-                                    xre[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, B, xre[t], 0, 0, 0);
-                                    xim[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, Bs, xim[t], 0, 0, 0);
-                                } else {
-                                    vre[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, B, vre[t], 0, 0, 0);
-                                    vim[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A, Bs, vim[t], 0, 0, 0);
-                                }
-                            }
-                        });
-                    });
-                } else {
-                    uintx4 f[R], gg[R];
-                    static_for<R>([&](auto bi) {
-                        constexpr int b = decltype(bi)::value;
-                        if constexpr ((useA >> b) & 1u) f[b] = *(const uintx4*)(buf + lds_off(32 * b + row, g));
-                        if constexpr ((useB >> b) & 1u) gg[b] = swapneg_i8(f[b]);
-                    });
-                    static_for<NW>([&](auto ti) {
-                        constexpr int t = decltype(ti)::value;
-                        constexpr int I = tile_I(R, T0 + t), J = tile_J(R, T0 + t);
-                        const frag_t A = __builtin_bit_cast(frag_t, f[I]);
-                        const frag_t B = __builtin_bit_cast(frag_t, f[J]);
-                        const frag_t Bs = __builtin_bit_cast(frag_t, gg[J]);
-                        vre[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, B, vre[t], 0, 0, 0);
-                        vim[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A, Bs, vim[t], 0, 0, 0);
-                    });
-                }
-            }
-        }
-        cur ^= 1;
-    }
-
-    // ---- diagonal tiles (FP16-split): Re += hl + hl^T, Im += hl - hl^T, through LDS ----
-    if constexpr (MODE == XM_FP16_SPLIT) {
-        __syncthreads();                      // every wave is done with the chunk buffers
-        constexpr int kTw = 2 * 32 * 33;      // floats per wave: two padded 32 x 32 tiles
-        float* tr = (float*)lds + W * kTw;
-        static_for<NW>([&](auto ti) {
-            constexpr int t = decltype(ti)::value;
-            constexpr int I = tile_I(R, T0 + t), J = tile_J(R, T0 + t);
-            if constexpr (kDiagHl && I == J) {
-                static_assert((W + 1) * kTw * 4 <= 2 * R * 32 * kRowB, "transpose area inside LDS");
-                const int col = lane & 31;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                    tr[row * 33 + col] = xre[t][r];
-                    tr[32 * 33 + row * 33 + col] = xim[t][r];
-                }
-                // the same wave reads the transpose back (its LDS operations complete in order)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                    vre[t][r] += xre[t][r] + tr[col * 33 + row];
-                    vim[t][r] += xim[t][r] - tr[32 * 33 + col * 33 + row];
-                }
-            }
-        });
-    }
-
-    // ---- epilogue: stored baselines s1 >= s2, all four polarisation products ----
-    if constexpr (NW > 0) {
-        const int64_t ch = blockIdx.x;
-        const int64_t B = (int64_t)a.S * (a.S + 1) / 2;
-        static_for<NW>([&](auto ti) {
-            constexpr int t = decltype(ti)::value;
-            constexpr int I = tile_I(R, T0 + t), J = tile_J(R, T0 + t);
-            const int b = 32 * J + (lane & 31);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int aa = 32 * I + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                if (aa < a.M && b < a.M) {
-                    const int s1 = aa >> 1, s2 = b >> 1;
-                    if (s1 >= s2) {
-                        const int64_t idx = (ch * B + (int64_t)s1 * (s1 + 1) / 2 + s2) * 4 + 2 * (aa & 1) + (b & 1);
-                        if constexpr (MODE == XM_FP16_SPLIT) {
-                            const float re = vre[t][r] * a.out_scale;
-                            const float im = aa == b ? 0.f : vim[t][r] * a.out_scale;
-                            ((float2*)a.vis)[idx] = make_float2(re, im);
-                        } else {
-                            ((int2*)a.vis)[idx] = make_int2(vre[t][r], aa == b ? 0 : vim[t][r]);
-                        }
-                    }
-                }
-            }
-        });
-    }
-}
-
-template <int MODE, int R>
-__global__ __launch_bounds__(256, 2) void xstage_mfma_kernel(XArgs a) {
-    __shared__ __attribute__((aligned(1024))) char lds[2 * R * 32 * kRowB];   // two chunk buffers
-    const int tid = threadIdx.x;
-    const char* chan = (const char*)a.chan + (int64_t)blockIdx.x * a.chan_stride;
-    switch (tid >> 6) {
-        case 0: xwave<MODE, R, 0>(a, chan, lds, tid); break;
-        case 1: xwave<MODE, R, 1>(a, chan, lds, tid); break;
-        case 2: xwave<MODE, R, 2>(a, chan, lds, tid); break;
-        default: xwave<MODE, R, 3>(a, chan, lds, tid); break;
-    }
-}
-
-template <int MODE>
-hipError_t launch_mode(const XArgs& a, hipStream_t st) {
-    const int R = (a.M + 31) / 32;
-    const dim3 grid((unsigned)a.n_chan), block(256);
-    switch (R) {
-        case 1: hipLaunchKernelGGL((xstage_mfma_kernel<MODE, 1>), grid, block, 0, st, a); break;
-        case 2: hipLaunchKernelGGL((xstage_mfma_kernel<MODE, 2>), grid, block, 0, st, a); break;
-        case 3: hipLaunchKernelGGL((xstage_mfma_kernel<MODE, 3>), grid, block, 0, st, a); break;
-        case 4: hipLaunchKernelGGL((xstage_mfma_kernel<MODE, 4>), grid, block, 0, st, a); break;
-        case 5: hipLaunchKernelGGL((xstage_mfma_kernel<MODE, 5>), grid, block, 0, st, a); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
 
 // ------------------------------------------------------------------ LDS ring ---
 // Chunks (one K block in FP32 and FP16-split mode, four in int8 mode; 256 bytes per row) stream
@@ -476,6 +206,269 @@ __device__ __forceinline__ void ring_loop(const XArgs& a, const XRing& q, const 
         body(buf, nch);
     }
     lds_barrier();                            // every wave is done with the chunks
+}
+
+// ------------------------------------------------------------------ MFMA forms ---
+// One workgroup of NWV waves per channel.  The lower triangle of 16 x 16 tiles (NB row blocks) goes
+// to ks_groups wave groups as runs of a column-major tile list; the waves of a group split the
+// k-steps of a stage among them, so that a few tiles keep every wave busy.
+// Bound by the channel's HBM stream and, with many channels, by the chip's power: both the stream
+// and the matrix pipes draw on it (24 stations x 2048 channels holds 1.70 GHz), so work that is not
+// needed costs time also where no pipe is full.  Hence tiles of 16 (48 inputs: 30 MFMAs of 16x16x32
+// per 16 samples against 28 of twice the length with tiles of 32), zeros for the padding rows and
+// two instead of three products on the diagonal.  Four waves per workgroup and two to four
+// workgroups per CU; with at most one channel per CU eight waves and the whole LDS as ring.
+// Groups are as few as the accumulators and fragments allow without spilling.
+// Measured against one workgroup of four waves with up to four 32 x 32 tiles each (waves idle below
+// 5 row blocks of 32), us, FP16-split: 24 st x 32 SB 604 -> 428 (5.7 TB/s); 48 x 16 640 -> 545;
+// 52 x 61 2905 -> 2240; 76 x 64 4030 -> 3780; 24 x 1 125 -> 49; 48 x 1 at 256 channels 54 -> 36.
+// int8: 24 x 32 143 -> 112; 76 x 64 944 -> 932.
+template <int MODE, int NB, int NWV> constexpr int ks_groups() {
+    if (NB <= 3) return 1;
+    if (NB <= 5) return NWV == 8 ? 2 : 1;
+    if (NB <= 7) return 2;
+    return NB == 8 && MODE == XM_INT8 ? 2 : 4;
+}
+template <int MODE, int NB, int NWV> constexpr int ks_per() {
+    return (tile_count(NB) + ks_groups<MODE, NB, NWV>() - 1) / ks_groups<MODE, NB, NWV>();
+}
+template <int MODE, int NB, int NWV, int G> constexpr int ks_tiles() {
+    const int left = tile_count(NB) - G * ks_per<MODE, NB, NWV>();
+    return left < ks_per<MODE, NB, NWV>() ? left : ks_per<MODE, NB, NWV>();
+}
+template <int NB, int NWV> constexpr int ks_lds() { return NWV == 8 ? 147456 : NB <= 2 ? 40960 : NB == 3 ? 53248 : 81920; }
+template <int NB, int NWV> constexpr int ks_waves_per_simd() { return NWV == 8 ? 2 : NB <= 2 ? 4 : NB == 3 ? 3 : 2; }
+// row blocks used by tiles [t0, t0 + n)
+constexpr unsigned ks_blocks(int NB, int t0, int n) {
+    unsigned m = 0;
+    for (int t = t0; t < t0 + n; ++t) m |= 1u << tile_I(NB, t) | 1u << tile_J(NB, t);
+    return m;
+}
+
+template <int MODE> struct KCfg;
+template <> struct KCfg<XM_FP16_SPLIT> {
+    static constexpr int kSteps = 2;          // k-steps of 16 samples per chunk
+    using acc_t = floatx4;
+};
+template <> struct KCfg<XM_INT8> {
+    static constexpr int kSteps = 4;          // k-steps of 32 samples per chunk
+    using acc_t = intx4;
+};
+
+// Halve the k parts of a group's sums: of waves p and p ^ half (half a power of two), the lower
+// keeps the first (N + 1) / 2 tiles and the upper the rest, each adding what the other sent through
+// LDS; the tiles a wave keeps move to the front and t_own follows.  Ends with a barrier.
+template <int N, class ACC>
+__device__ __forceinline__ void ks_halve(ACC* re, ACC* im, ACC* area, int kpart, int half, int stride, int lane, int& t_own, int& n_own) {
+    constexpr int H = (N + 1) / 2;
+    const bool upper = (kpart & half) != 0;
+    ACC* mine = area + lane;                                            // this wave's outgoing tiles
+    const ACC* theirs = area + (upper ? -half : half) * stride + lane;  // the partner's
+    if (upper) {
+#pragma unroll
+        for (int t = 0; t < H; ++t) { mine[2 * t * 64] = re[t]; mine[(2 * t + 1) * 64] = im[t]; }
+#pragma unroll
+        for (int t = H; t < N; ++t) { re[t - H] = re[t]; im[t - H] = im[t]; }
+    } else {
+#pragma unroll
+        for (int t = H; t < N; ++t) { mine[2 * (t - H) * 64] = re[t]; mine[(2 * (t - H) + 1) * 64] = im[t]; }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int t = 0; t < H; ++t) {
+        if (t < N - H || !upper) {
+            re[t] += theirs[2 * t * 64];
+            im[t] += theirs[(2 * t + 1) * 64];
+        }
+    }
+    t_own += upper ? H : 0;
+    n_own = upper ? n_own - H : min(n_own, H);
+    lds_barrier();
+}
+template <int N, int P, class ACC>
+__device__ __forceinline__ void ks_reduce(ACC* re, ACC* im, ACC* area, int kpart, int stride, int lane, int& t_own, int& n_own) {
+    if constexpr (P > 1) {
+        ks_halve<N>(re, im, area, kpart, P / 2, stride, lane, t_own, n_own);
+        ks_reduce<(N + 1) / 2, P / 2>(re, im, area, kpart, stride, lane, t_own, n_own);
+    }
+}
+constexpr int ks_left(int n, int parts) { return parts > 1 ? ks_left((n + 1) / 2, parts / 2) : n; }
+
+template <int MODE, int NB, int NWV, int G>
+__device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const char* __restrict__ chan, char* lds, int tid) {
+    using acc_t = typename KCfg<MODE>::acc_t;
+    constexpr int kSteps = KCfg<MODE>::kSteps;
+    constexpr int kTG = ks_groups<MODE, NB, NWV>(), kPer = ks_per<MODE, NB, NWV>(), T0 = G * kPer, NT = ks_tiles<MODE, NB, NWV, G>(), kKP = NWV / kTG;
+    constexpr unsigned kUsed = ks_blocks(NB, T0, NT);
+    constexpr bool kDiagHl = MODE == XM_FP16_SPLIT && kKP == 1;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, kpart = wave / kTG;
+    const int row = lane & 15, kg = lane >> 4;
+
+    acc_t re[kPer], im[kPer];
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) re[t] = im[t] = acc_t{};
+    acc_t xre[kDiagHl ? kPer : 1], xim[kDiagHl ? kPer : 1];             // h l^T of diagonal tiles
+#pragma unroll
+    for (int t = 0; t < (kDiagHl ? kPer : 1); ++t) xre[t] = xim[t] = acc_t{};
+    // the last row block's padding rows read zeros kept behind the ring (a zero operand also spares
+    // the matrix pipes' power)
+    const bool pad = 16 * (NB - 1) + row >= a.M;
+    const char* zeros = lds + ks_lds<NB, NWV>() - 256;
+    if (tid < 16) *(uint4*)(lds + ks_lds<NB, NWV>() - 256 + tid * 16) = make_uint4(0, 0, 0, 0);
+
+    ring_loop<MODE, NWV>(a, q, chan, lds, tid, [&](char* buf, int nch) {
+        for (int id = kpart; id < nch * kSteps; id += kKP) {
+            const char* base = buf + (id / kSteps) * q.chunk_b + row * kRowB + (((4 * (id % kSteps) + kg) ^ row) << 4);
+            const char* last = pad ? zeros : base + 16 * (NB - 1) * kRowB;
+            if constexpr (MODE == XM_FP16_SPLIT) {
+                const int to_lo = pad ? 0 : (base - buf) & 128 ? -128 : 128;       // granule 8 + g
+                const char* base_lo = buf + ((base - buf) ^ 128);
+                uintx4 fh[NB], fl[NB];
+                static_for<NB>([&](auto bi) {
+                    constexpr int b = decltype(bi)::value;
+                    if constexpr ((kUsed >> b) & 1u) {
+                        fh[b] = *(const uintx4*)(b == NB - 1 ? last : base + 16 * b * kRowB);
+                        fl[b] = *(const uintx4*)(b == NB - 1 ? last + to_lo : base_lo + 16 * b * kRowB);
+                    }
+                });
+                static_for<3>([&](auto pi) {
+                    constexpr int pr = decltype(pi)::value;
+                    static_for<NT>([&](auto t_) {
+                        constexpr int t = decltype(t_)::value;
+                        constexpr int I = tile_I(NB, T0 + t), J = tile_J(NB, T0 + t);
+                        if constexpr (!(I == J && pr == 2)) {
+                            const half8 A = __builtin_bit_cast(half8, pr == 2 ? fl[I] : fh[I]);
+                            half8 B = __builtin_bit_cast(half8, pr == 1 ? fl[J] : fh[J]);
+                            if constexpr (I == J && pr == 1 && !kDiagHl) B = B + B;
+                            const half8 Bs = __builtin_bit_cast(half8, swapneg_f16(__builtin_bit_cast(uintx4, B)));
+                            acc_t& R = I == J && pr == 1 && kDiagHl ? xre[kDiagHl ? t : 0] : re[t];
+                            acc_t& Q = I == J && pr == 1 && kDiagHl ? xim[kDiagHl ? t : 0] : im[t];
+                            R = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, B, R, 0, 0, 0);
+                            Q = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, Bs, Q, 0, 0, 0);
+                        }
+                    });
+                });
+            } else {
+                uintx4 f[NB];
+                static_for<NB>([&](auto bi) {
+                    constexpr int b = decltype(bi)::value;
+                    if constexpr ((kUsed >> b) & 1u) f[b] = *(const uintx4*)(b == NB - 1 ? last : base + 16 * b * kRowB);
+                });
+                static_for<NT>([&](auto t_) {
+                    constexpr int t = decltype(t_)::value;
+                    constexpr int I = tile_I(NB, T0 + t), J = tile_J(NB, T0 + t);
+                    const intx4 A = __builtin_bit_cast(intx4, f[I]), B = __builtin_bit_cast(intx4, f[J]);
+                    const intx4 Bs = __builtin_bit_cast(intx4, swapneg_i8(f[J]));
+                    re[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B, re[t], 0, 0, 0);
+                    im[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, Bs, im[t], 0, 0, 0);
+                });
+            }
+        }
+    });
+
+    // ---- sums over the k parts; every wave ends with a share of its group's tiles ----
+    constexpr int kStride = kTG * ((kPer + 1) / 2) * 2 * 64;            // accumulators between k parts' areas
+    static_assert(kKP == 1 || kKP * kStride * 16 <= ks_lds<NB, NWV>(), "partial sums inside LDS");
+    int t_own = T0, n_own = NT;
+    ks_reduce<kPer, kKP>(re, im, (acc_t*)lds + kpart * kStride + G * (kStride / kTG), kpart, kStride, lane, t_own, n_own);
+
+    // ---- stored baselines s1 >= s2, all four polarisation products ----
+    const int64_t ch = blockIdx.x;
+    const int64_t n_bl = (int64_t)a.S * (a.S + 1) / 2;
+    float* tr = (float*)lds + wave * (2 * 16 * 17);
+#pragma unroll
+    for (int t = 0; t < ks_left(kPer, kKP); ++t) {
+        if (t >= n_own) continue;
+        int J = 0, I = t_own + t;                                       // tile t_own + t of the column-major list
+        while (I >= NB - J) { I -= NB - J; ++J; }
+        I += J;
+        // lane: column b, rows aa0 .. aa0 + 3 (both polarisations of stations aa0 / 2 and aa0 / 2 + 1)
+        const int b = 16 * J + row, aa0 = 16 * I + 4 * kg;
+        acc_t vr = re[t], vi = im[t];
+        if constexpr (MODE == XM_FP16_SPLIT) {
+            if (I == J) {
+                // (W + W^T) / 2 and (W - W^T) / 2, or h h^T + X + X^T and h h^T + X - X^T with
+                // X = h l^T; the same wave reads its transpose back (its LDS operations complete in
+                // order)
+                const acc_t wr = kDiagHl ? xre[kDiagHl ? t : 0] : vr, wi = kDiagHl ? xim[kDiagHl ? t : 0] : vi;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    tr[(4 * kg + r) * 17 + row] = wr[r];
+                    tr[16 * 17 + (4 * kg + r) * 17 + row] = wi[r];
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float sr = wr[r] + tr[row * 17 + 4 * kg + r], si = wi[r] - tr[16 * 17 + row * 17 + 4 * kg + r];
+                    vr[r] = kDiagHl ? vr[r] + sr : 0.5f * sr;
+                    vi[r] = kDiagHl ? vi[r] + si : 0.5f * si;
+                }
+            }
+            vr *= a.out_scale;
+            vi *= a.out_scale;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (aa0 + r == b) vi[r] = 0;
+        // lanes of an even and the next odd column exchange, so that each stores two neighbouring
+        // polarisation products (16 bytes): even columns XX, XY, odd columns YX, YY
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const uintx4 wr = __builtin_bit_cast(uintx4, vr), wi = __builtin_bit_cast(uintx4, vi);
+            const unsigned r0 = wr[2 * u], i0 = wi[2 * u], r1 = wr[2 * u + 1], i1 = wi[2 * u + 1];
+            const bool odd = (row & 1) != 0;
+            const unsigned sr = odd ? r0 : r1, si = odd ? i0 : i1;      // what the neighbour stores
+            const unsigned gr = __builtin_amdgcn_mov_dpp(sr, 0xb1, 0xf, 0xf, true);   // quad_perm 1, 0, 3, 2
+            const unsigned gi = __builtin_amdgcn_mov_dpp(si, 0xb1, 0xf, 0xf, true);
+            const int s1 = (aa0 >> 1) + u, s2 = b >> 1;
+            if (s1 < a.S && s2 <= s1) {
+                const uintx4 v = odd ? uintx4{gr, gi, r1, i1} : uintx4{r0, i0, gr, gi};
+                ((uintx4*)a.vis)[(ch * n_bl + (int64_t)s1 * (s1 + 1) / 2 + s2) * 2 + (odd ? 1 : 0)] = v;
+            }
+        }
+    }
+}
+
+template <int MODE, int NB, int NWV>
+__global__ __launch_bounds__(64 * NWV, (ks_waves_per_simd<NB, NWV>())) void xstage_ksplit_kernel(XArgs a, XRing q) {
+    __shared__ __attribute__((aligned(1024))) char lds[ks_lds<NB, NWV>()];
+    const int tid = threadIdx.x;
+    const char* chan = (const char*)a.chan + (int64_t)blockIdx.x * a.chan_stride;
+    const int g = __builtin_amdgcn_readfirstlane(tid >> 6) % ks_groups<MODE, NB, NWV>();
+    static_for<ks_groups<MODE, NB, NWV>()>([&](auto gi) {
+        constexpr int G = decltype(gi)::value;
+        if (g == G) xks_wave<MODE, NB, NWV, G>(a, q, chan, lds, tid);
+    });
+}
+
+template <int MODE, int NB, int NWV>
+void launch_ksplit(const XArgs& a, hipStream_t st) {
+    // a stage holds a multiple of the k-steps that the waves of a group share
+    constexpr int parts = NWV / ks_groups<MODE, NB, NWV>(), mult = parts > KCfg<MODE>::kSteps ? parts / KCfg<MODE>::kSteps : 1;
+    const XRing q = make_ring(MODE, a, NWV, ks_lds<NB, NWV>() - 256, (16 * NB - (a.M + 3) / 4 * 4) * kRowB, mult);
+    hipLaunchKernelGGL((xstage_ksplit_kernel<MODE, NB, NWV>), dim3((unsigned)a.n_chan), dim3(64 * NWV), 0, st, a, q);
+}
+template <int MODE, int NB>
+void launch_ksplit(const XArgs& a, hipStream_t st) {
+    if (a.n_chan <= kCUs) launch_ksplit<MODE, NB, 8>(a, st);
+    else launch_ksplit<MODE, NB, 4>(a, st);
+}
+
+template <int MODE>
+hipError_t launch_mode(const XArgs& a, hipStream_t st) {
+    switch ((a.M + 15) / 16) {
+        case 1: launch_ksplit<MODE, 1>(a, st); break;
+        case 2: launch_ksplit<MODE, 2>(a, st); break;
+        case 3: launch_ksplit<MODE, 3>(a, st); break;
+        case 4: launch_ksplit<MODE, 4>(a, st); break;
+        case 5: launch_ksplit<MODE, 5>(a, st); break;
+        case 6: launch_ksplit<MODE, 6>(a, st); break;
+        case 7: launch_ksplit<MODE, 7>(a, st); break;
+        case 8: launch_ksplit<MODE, 8>(a, st); break;
+        case 9: launch_ksplit<MODE, 9>(a, st); break;
+        case 10: launch_ksplit<MODE, 10>(a, st); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ plain FP32 form ---
