@@ -56,8 +56,8 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 template <int KS>
 constexpr int beam_waves() { return KS <= 6 ? 3 : 2; }
 
-template <int KS, int NS, bool VOLT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(beam_waves<KS>()))) void beam_kernel(BeamArgs a) {
+template <int KS, int NS, bool VOLT, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(beam_waves<KS>()))) void beam_kernel(BeamArgs a) {
     // one staged block = the channelised K block with its rows regrouped by polarisation:
     // [plane][pol][station][32 samples] words, 8 KS station rows per polarisation (padding rows
     // stay zero), so that consecutive stations of one polarisation are consecutive rows
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(beam_waves<
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t ch = blockIdx.x;                      // sb * C + c
     const int sb = (int)(ch / a.C), c = (int)(ch % a.C);
-    const int bt = blockIdx.y * 4 + wv;                 // beam tile of this wave
+    const int bt = blockIdx.y * NW + wv;                // beam tile of this wave
     const bool do_inc = a.incoherent != nullptr && blockIdx.y == 0;
     const char* chan = (const char*)a.chan + ch * a.chan_stride;
 
@@ -113,12 +113,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(beam_waves<
     const int wvu = __builtin_amdgcn_readfirstlane(wv);
     const int lst = lane >> 3;
     const unsigned lane_off = (unsigned)(lst * 256 + (lane & 7) * 16);
-    constexpr int kIt = (2 * n_inst + 3) / 4;           // instructions per wave and block
+    constexpr int kIt = (2 * n_inst + NW - 1) / NW;     // instructions per wave and block
     int src_off[kIt], dst_off[kIt];                     // wave-uniform, fixed for the kernel
     bool live[kIt];
 #pragma unroll
     for (int it = 0; it < kIt; ++it) {
-        const int i = wvu + 4 * it;
+        const int i = wvu + NW * it;
         const int pl = i / n_inst, j = i % n_inst;
         const int pol = (8 * j) / kS8, st0 = (8 * j) % kS8;
         src_off[it] = (pl * M + 2 * st0 + pol) * 128;
@@ -136,12 +136,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(beam_waves<
     // zero the padding rows (stations S .. kS8 - 1 of each polarisation) of both planes of both
     // buffers once
     const int npad = kS8 - a.S;
-    for (int i = tid; i < 2 * 2 * 2 * npad * kBT; i += 256) {
+    for (int i = tid; i < 2 * 2 * 2 * npad * kBT; i += 64 * NW) {
         const int w = i % kBT, r = (i / kBT) % npad, pol = (i / (kBT * npad)) % 2, pl = (i / (kBT * npad * 2)) % 2,
                   bufi = i / (kBT * npad * 4);
         sm[bufi * kBuf + pl * kPlaneW + (pol * kS8 + a.S + r) * kBT + w] = 0u;
     }
-    const int n_kb = a.n_kb;
+    const int kb0 = blockIdx.z * a.kb_part, n_kb = min(a.n_kb, kb0 + a.kb_part);   // this part of the time
     const float vscale = a.vscale;
     constexpr int nS = NS;                              // Stokes parameters: 1 (I) or 4 (IQUV)
     const float sscale = vscale * vscale;               // Stokes are quadratic in the voltages
@@ -178,28 +178,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(beam_waves<
         if (a.n_int <= kBT || tstart % a.n_int == 0) *o = v;
         else *o += v;
     };
-    // incoherent partial sums of a block, [buffer][wave][sample][stokes]: wave w holds the sums
+    // incoherent partial sums of a block, [buffer][part][sample][stokes]: part w holds the sums
     // over the stations of groups 2w and 2w + 1 (station s is in group s % 8)
     __shared__ float inc_p[2][4][kBT][NS];
     // after a barrier: the four partial sums of each sample of block kbp in a fixed order, then
     // the sums over windows of g samples (32 lanes per Stokes parameter, from wave 0 on)
     auto inc_finish = [&](int kbp) {
-        const int idx = wv * 64 + lane, k = idx / kBT, tl = idx % kBT;
-        if (k >= NS) return;
-        const int t = kbp * kBT + tl;
-        const int bi = kbp & 1;
-        float x = t < a.n_c ? ((inc_p[bi][0][tl][k] + inc_p[bi][1][tl][k]) + (inc_p[bi][2][tl][k] + inc_p[bi][3][tl][k])) * sscale : 0.f;
-        for (int m = 1; m < g; m <<= 1) x += __shfl_xor(x, m, 64);
-        if ((tl & (g - 1)) == 0 && t < a.n_c) put(io_ch + out_index(t) * nS + k, t, x);
+        for (int idx = tid; idx < NS * kBT; idx += 64 * NW) {
+            const int k = idx / kBT, tl = idx % kBT;
+            const int t = kbp * kBT + tl;
+            const int bi = kbp & 1;
+            float x = t < a.n_c ? ((inc_p[bi][0][tl][k] + inc_p[bi][1][tl][k]) + (inc_p[bi][2][tl][k] + inc_p[bi][3][tl][k])) * sscale : 0.f;
+            for (int m = 1; m < g; m <<= 1) x += __shfl_xor(x, m, 64);
+            if ((tl & (g - 1)) == 0 && t < a.n_c) put(io_ch + out_index(t) * nS + k, t, x);
+        }
     };
 
     __syncthreads();
-    if (n_kb > 0) issue(0, sm);
-    for (int kb = 0; kb < n_kb; ++kb) {
+    if (kb0 < n_kb) issue(kb0, sm + (kb0 & 1) * kBuf);
+    for (int kb = kb0; kb < n_kb; ++kb) {
         unsigned* buf = sm + (kb & 1) * kBuf;
         __builtin_amdgcn_s_waitcnt(0);                  // this wave's transfers of block kb have landed
         __syncthreads();                                // ... and everyone's; buffer kb+1 is free
-        if (do_inc && kb > 0) inc_finish(kb - 1);
+        if (do_inc && kb > kb0) inc_finish(kb - 1);
         if (kb + 1 < n_kb) issue(kb + 1, sm + ((kb + 1) & 1) * kBuf);
         const int tb = kb * kBT;
 
@@ -337,12 +338,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(beam_waves<
             }
         }
 
-        // ---- incoherent: lane (half hb, sample tl) of wave w sums stations 8 ks + 2 w + hb; one
+        // ---- incoherent: lane (half hb, sample tl) of part w sums stations 8 ks + 2 w + hb; one
         // read of a wave covers two station rows of 32 samples.  For Stokes I every read is at a
         // fixed offset from one lane base (the hi and lo words of a station row in one paired
         // read), the padding rows (stations S .. 8 KS - 1) being zero and adding nothing ----
-        if (do_inc) {
-            const int tl = lane & 31, grp = 2 * wv + hb;
+        for (int w = wv; do_inc && w < 4; w += NW) {
+            const int tl = lane & 31, grp = 2 * w + hb;
             const unsigned* q = buf + grp * kBT + tl;
             float acc[NS] = {};
 #pragma unroll
@@ -379,27 +380,76 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(beam_waves<
 #pragma unroll
             for (int k = 0; k < NS; ++k) {
                 const float x = add_halves(acc[k]);
-                if (hb == 0) inc_p[kb & 1][wv][tl][k] = x;
+                if (hb == 0) inc_p[kb & 1][w][tl][k] = x;
             }
         }
     }
-    if (do_inc && n_kb > 0) {
+    if (do_inc && n_kb > kb0) {
         __syncthreads();
         inc_finish(n_kb - 1);
     }
 }
 
+// Waves per workgroup (beam tiles of 32 each) and K blocks per workgroup.
+//  - Four waves, so that the staging and the incoherent sums are shared; with few stations a block
+//    is small and these are cheap, and a wave without a beam tile only takes up one of the twelve
+//    places of a CU: one or two waves up to 16 stations (5 stations, 16 beams, us: 203 with four
+//    waves, 157 with two, 117 with one; 13 stations, 40 beams, IQUV: 102 / 87 / 136; 48 stations,
+//    32 beams: 168 / 191 / 224), two up to 24 stations for Stokes I.
+//  - Few channels leave CUs idle or a long last round: below two rounds of resident workgroups the
+//    channel's time is split into parts of whole windows and at least four blocks, as many as give
+//    the least rounds per part; each part repeats the weights (about 4 % of a part).  30 stations,
+//    128 channels of 3072 samples: 215 us in one part, 112 in two, 64 in four; 48 stations, 1024
+//    channels: 160 / 143 / 150; 24 stations, 1536 channels of 7 blocks: 38 / 39 / 47.
+template <int KS, int NS>
+int beam_nw(int tiles) {
+    if (KS == 1 && tiles == 1) return 1;
+    return tiles <= 2 && (KS <= 2 || (KS == 3 && NS == 1)) ? 2 : 4;
+}
+int beam_kb_part(const BeamArgs& a, int64_t groups, int resident) {
+    const int unit = a.n_int > kBT ? a.n_int / kBT : 1;                 // blocks of a window
+    int best = (a.n_kb + unit - 1) / unit * unit;                       // one part
+    if (groups >= 2 * resident) return best;
+    double least = 1e30;
+    for (int parts = 1; parts <= 16; ++parts) {
+        const int per = ((a.n_kb + parts - 1) / parts + unit - 1) / unit * unit;
+        if (parts > 1 && per < 4) break;
+        const int64_t n = (a.n_kb + per - 1) / per;
+        const double t = (double)((groups * n + resident - 1) / resident) * per * (1.0 + 0.04 * (double)(n - 1));
+        if (t < least) { least = t; best = per; }
+    }
+    return best;
+}
+
 // VOLT: the voltage output is compiled in only where voltages are asked for
+template <int KS, int NS, bool VOLT>
+void launch_vs(BeamArgs a, hipStream_t st) {
+    const int tiles = (a.NB + 31) / 32, nw = beam_nw<KS, NS>(tiles), gy = (tiles + nw - 1) / nw;
+    a.kb_part = beam_kb_part(a, (int64_t)a.n_chan * gy, kCUs * 4 * beam_waves<KS>() / nw);
+    const dim3 grid((unsigned)a.n_chan, (unsigned)gy, (unsigned)((a.n_kb + a.kb_part - 1) / a.kb_part)), block(64 * nw);
+    if constexpr (KS == 1) {
+        if (nw == 1) {
+            hipLaunchKernelGGL((beam_kernel<KS, NS, VOLT, 1>), grid, block, 0, st, a);
+            return;
+        }
+    }
+    if constexpr (KS <= 2 || (KS == 3 && NS == 1)) {
+        if (nw == 2) {
+            hipLaunchKernelGGL((beam_kernel<KS, NS, VOLT, 2>), grid, block, 0, st, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((beam_kernel<KS, NS, VOLT, 4>), grid, block, 0, st, a);
+}
 template <int KS>
 hipError_t launch_ks(const BeamArgs& a, hipStream_t st) {
-    const dim3 grid((unsigned)a.n_chan, (unsigned)((a.NB + 127) / 128)), block(256);
     const bool v = a.voltages != nullptr;
     if (a.n_stokes == 1) {
-        if (v) hipLaunchKernelGGL((beam_kernel<KS, 1, true>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((beam_kernel<KS, 1, false>), grid, block, 0, st, a);
+        if (v) launch_vs<KS, 1, true>(a, st);
+        else launch_vs<KS, 1, false>(a, st);
     } else {
-        if (v) hipLaunchKernelGGL((beam_kernel<KS, 4, true>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((beam_kernel<KS, 4, false>), grid, block, 0, st, a);
+        if (v) launch_vs<KS, 4, true>(a, st);
+        else launch_vs<KS, 4, false>(a, st);
     }
     return hipGetLastError();
 }

@@ -77,6 +77,7 @@ struct BeamArgs {
     double df;               // channel width (Hz)
     int32_t C, S, NB, n_c, n_kb, n_chan, n_int, n_stokes;
     int32_t vstride;         // beams per voltage row (>= NB)
+    int32_t kb_part;         // K blocks per workgroup (whole windows)
     float vscale;            // 2^-k: undoes the FP16-split prescale
 };
 
