@@ -28,8 +28,9 @@
 // every such run on one line).  The workgroup walks the groups of 16 beams of its row, loading
 // the next group into registers while it transforms the current one; the twiddles come from a
 // 2 KB LDS table.  Stokes parameters at C_out = 16 are summed in registers (the output channel
-// is the thread's digit, the polarisations sit 16 lanes apart); at other C_out the outputs go
-// through LDS to be summed across threads.  Memory-bound: one read of the voltages, one write
+// is the thread's digit, the polarisations sit 16 lanes apart); at other C_out long windows are
+// summed in registers as far as one thread holds them and then through LDS, short ones from the
+// outputs in LDS.  Memory-bound: one read of the voltages, one write
 // of the outputs.
 #include "cobalt_internal.h"
 
@@ -128,7 +129,9 @@ __device__ __forceinline__ void dft(float (&re)[N], float (&im)[N]) {
     static_assert(N <= 16, "transforms of up to 16 points in registers");
 }
 
-template <int COUT, int NS>
+// LONG: the form for Stokes windows of several n1 (a kernel of its own: with both forms in one the
+// registers of 4 waves per SIMD do not suffice)
+template <int COUT, int NS, bool LONG>
 __global__ __launch_bounds__(kXThreads, 4) void beam_transform_kernel(TfArgs a) {
     // exchange rows 16 t + c1 (Z of digit c1 for thread t), later output slots s; 32 transforms
     __shared__ float2 buf[kXC * kNF];
@@ -277,6 +280,71 @@ __global__ __launch_bounds__(kXThreads, 4) void beam_transform_kernel(TfArgs a) 
                     for (int k = 0; k < NS; ++k) acc[k] = 0.f;
                 }
             }
+        } else if constexpr (NS > 0 && LONG) {
+            // Windows longer than one n1.  Thread t = d holds slots 16 n1 + t, i.e. output samples
+            // g = Q n1 + q of channel c' (t = COUT q + c'), and a window covers whole runs of n1 and
+            // all q: the runs are summed in registers, the q values through LDS (the other branch
+            // puts the voltages into LDS and leaves each window to one thread, 64 threads of 512 at
+            // c_out = 1, n_int = 64; 8 subbands, 61 beams, IQUV, us: c_out 1 n_int 64 488 -> 419 and
+            // n_int 256 977 -> 389, 2 / 128 604 -> 373, 4 / 64 451 -> 347, 8 / 32 421 -> 367;
+            // 2 subbands, 20 beams, 1 / 256 55 -> 16).  Swapping the real part's
+            // odd rows of 16 lanes (polarisation 1) with the imaginary part's even rows leaves both
+            // polarisations' real parts in the even rows and their imaginary parts in the odd rows,
+            // so that |X|^2, |Y|^2 and Re X conj Y are one FMA each per lane, and the opposite swap
+            // gives Im X conj Y (even minus odd rows); the two rows' sums meet once per window.
+            constexpr int Q = 16 / COUT;
+            const int run = a.n_int / Q;
+            float* stage = (float*)buf;                            // [run of n1][stokes][digit][beam]
+            float* mine = stage + ((NS == 4 ? 2 * p : 0) * 16 + d) * kBG + b;
+            float acc[4] = {0.f, 0.f, 0.f, 0.f};
+            auto add_pols = [](float v) {
+                const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+                return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+            };
+            __syncthreads();                                       // every thread has read its Z rows
+#pragma unroll
+            for (int n1 = 0; n1 < 16; ++n1) {
+                const int i = bitrev<16>(n1);
+                if constexpr (NS == 1) {
+                    acc[0] = fmaf(xr[i], xr[i], acc[0]);
+                    acc[0] = fmaf(xi[i], xi[i], acc[0]);
+                } else {
+                    const auto s0 = __builtin_amdgcn_permlane16_swap(__float_as_uint(xr[i]), __float_as_uint(xi[i]), false, false);
+                    const auto s1 = __builtin_amdgcn_permlane16_swap(__float_as_uint(xi[i]), __float_as_uint(xr[i]), false, false);
+                    const float X = __uint_as_float(s0[0]), Y = __uint_as_float(s0[1]), Xo = __uint_as_float(s1[0]);
+                    acc[0] = fmaf(X, X, acc[0]);
+                    acc[1] = fmaf(Y, Y, acc[1]);
+                    acc[2] = fmaf(X, Y, acc[2]);
+                    acc[3] = fmaf(Xo, Y, acc[3]);
+                }
+                if (((n1 + 1) & (run - 1)) == 0) {                 // the run's last sample
+                    if constexpr (NS == 1) {
+                        const float v = add_pols(acc[0]);
+                        if (p == 0) *mine = v;
+                    } else {
+                        const float xx = add_pols(acc[0]), yy = add_pols(acc[1]);
+                        const float u = add_pols(acc[2]), v = add_pols(p ? -acc[3] : acc[3]);
+                        // even rows keep I and Q, odd rows U and V
+                        mine[0] = p ? 2.f * u : xx + yy;
+                        mine[16 * kBG] = p ? 2.f * v : xx - yy;
+                    }
+                    mine += NS * 16 * kBG;
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) acc[k] = 0.f;
+                }
+            }
+            __syncthreads();
+            const int per_row = (kXC / COUT) >> nint_log2;         // Stokes samples per row and channel
+            float* __restrict__ so = (float*)a.sout + (((int64_t)sb * a.n_c + j) * per_row * COUT) * NS * a.NB + bg * kBG;
+            for (int it = tid; it < per_row * COUT * NS * kBG; it += kXThreads) {
+                const int bb = it % kBG, r = it / kBG;
+                const int k = r % NS, cc = (r / NS) % COUT, kn = r / (NS * COUT);
+                const float* src = stage + ((kn * NS + k) * 16 + cc) * kBG + bb;
+                float sum = 0.f;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) sum += src[q * COUT * kBG];
+                if (bg * kBG + bb < a.NB) so[((int64_t)(kn * COUT + cc) * NS + k) * a.NB + bb] = sum;
+            }
         } else if constexpr (NS > 0) {
             // sums across threads: the outputs go to LDS as slot rows, then one thread per
             // (Stokes sample, output channel, beam) adds its n_int samples
@@ -320,13 +388,28 @@ __global__ __launch_bounds__(kXThreads, 4) void beam_transform_kernel(TfArgs a) 
     }
 }
 
+// Windows of two n1 or more for Stokes I; of four or more for IQUV, whose sums over the polarisations
+// at each window's end cost more than they save in windows of two (20 beams, c_out 4, n_int 8: 16.9 us
+// against 19.3 us; c_out 2, n_int 16: 17.0 against 18.8).
+template <int COUT, int NS>
+void launch_stokes(const TfArgs& a, hipStream_t st) {
+    const dim3 grid((unsigned)((int64_t)a.SB * a.n_c)), block(kXThreads);
+    if constexpr (COUT < 16) {
+        if (a.n_int >= (NS == 1 ? 2 : 4) * (16 / COUT)) {
+            hipLaunchKernelGGL((beam_transform_kernel<COUT, NS, true>), grid, block, 0, st, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((beam_transform_kernel<COUT, NS, false>), grid, block, 0, st, a);
+}
 template <int COUT>
 hipError_t launch_cout(const TfArgs& a, hipStream_t st) {
-    const dim3 grid((unsigned)((int64_t)a.SB * a.n_c)), block(kXThreads);
     switch (a.sout ? a.n_stokes : 0) {
-        case 0: hipLaunchKernelGGL((beam_transform_kernel<COUT, 0>), grid, block, 0, st, a); break;
-        case 1: hipLaunchKernelGGL((beam_transform_kernel<COUT, 1>), grid, block, 0, st, a); break;
-        case 4: hipLaunchKernelGGL((beam_transform_kernel<COUT, 4>), grid, block, 0, st, a); break;
+        case 0:
+            hipLaunchKernelGGL((beam_transform_kernel<COUT, 0, false>), dim3((unsigned)((int64_t)a.SB * a.n_c)), dim3(kXThreads), 0, st, a);
+            break;
+        case 1: launch_stokes<COUT, 1>(a, st); break;
+        case 4: launch_stokes<COUT, 4>(a, st); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
