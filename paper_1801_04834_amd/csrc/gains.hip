@@ -5,9 +5,13 @@
 // stored visibility:  V'_ab = g_a conj(g_b) V0_ab.  For a real loss with upstream gradient
 // G = dL/dRe V' + i dL/dIm V', the gradient with respect to g_k (same convention) is
 //     sum_{entries with b = k} conj(G_ab) g_a V0_ab + sum_{entries with a = k} G_ab g_b conj(V0_ab).
-// Both kernels read the visibilities once per use and are bandwidth-bound; the adjoint gives
-// each input of a channel to one thread and sums its entries in a fixed order (no atomics,
-// bit-reproducible).
+// Both kernels are bandwidth-bound passes over the visibilities in their own order.  With
+// P = G conj(V0) the gradient is a product with the Hermitian matrix whose stored half P is:
+//     grad_a += P_ab g_b,    grad_b += conj(P_ab) g_a,
+// so the adjoint reads every entry once: a workgroup walks the baselines (s1, 0 .. s1) of a channel,
+// thread (s2, q) keeping the column sums of its input in registers and the row sums going through a
+// reduction over the threads of equal p1.  No atomics; the order of the sums is fixed
+// (bit-reproducible).
 #include "cobalt_internal.h"
 
 namespace cobalt {
@@ -18,74 +22,109 @@ __device__ __forceinline__ float2 cmul(float2 x, float2 y) {
 }
 __device__ __forceinline__ float2 cconj(float2 x) { return make_float2(x.x, -x.y); }
 
-__global__ __launch_bounds__(256) void apply_gains_kernel(const float2* __restrict__ vis0, const float2* __restrict__ gains,
-                                                          float2* __restrict__ vis, int64_t n_entries, int B, int M) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= n_entries) return;
-    const int q = (int)(e & 3);
-    const int64_t rest = e >> 2;
-    const int bl = (int)(rest % B);
-    const int64_t ch = rest / B;
+// Two neighbouring entries (one station pair and p1) per thread: 16-byte loads and stores, no 64-bit
+// division (48 stations, 1024 channels: 17.2 -> 13.3 us; 76 stations: 40 -> 30).
+__global__ __launch_bounds__(256) void apply_gains_kernel(const float4* __restrict__ vis0, const float2* __restrict__ gains,
+                                                          float4* __restrict__ vis, int B, int M, int per_ch) {
+    const int64_t ch = blockIdx.x / per_ch;
+    const int e = (int)(blockIdx.x % per_ch) * 256 + threadIdx.x;      // baseline * 2 + p1
+    if (e >= 2 * B) return;
+    const int bl = e >> 1, p1 = e & 1;
     int s1 = (int)((sqrtf(8.f * bl + 1.f) - 1.f) * 0.5f);
     while (s1 * (s1 + 1) / 2 > bl) --s1;
     while ((s1 + 1) * (s1 + 2) / 2 <= bl) ++s1;
     const int s2 = bl - s1 * (s1 + 1) / 2;
-    const float2 ga = gains[ch * M + 2 * s1 + (q >> 1)];
-    const float2 gb = gains[ch * M + 2 * s2 + (q & 1)];
-    vis[e] = cmul(cmul(ga, cconj(gb)), vis0[e]);
+    const float2* g = gains + ch * M;
+    const float2 ga = g[2 * s1 + p1], g0 = g[2 * s2], g1 = g[2 * s2 + 1];
+    const float4 v = vis0[ch * 2 * B + e];
+    const float2 x = cmul(cmul(ga, cconj(g0)), make_float2(v.x, v.y)), y = cmul(cmul(ga, cconj(g1)), make_float2(v.z, v.w));
+    vis[ch * 2 * B + e] = make_float4(x.x, x.y, y.x, y.y);
 }
 
-__global__ __launch_bounds__(256) void apply_gains_adjoint_kernel(const float2* __restrict__ vis0, const float2* __restrict__ gains,
+// v of this lane plus those of all lanes of the wave with the same lane bit 1
+__device__ __forceinline__ float add_same_p1(float v) {
+    v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xb1, 0xf, 0xf, true));   // lane ^ 1
+    v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x124, 0xf, 0xf, true));  // row rotated by 4
+    v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x128, 0xf, 0xf, true));  // row rotated by 8
+    const auto r16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
+    const auto r32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
+}
+
+// One workgroup of >= 4 S threads per channel: thread j = 4 s2 + q, q = 2 p1 + p2 (the entries of a
+// row s1 are 4 (s1 + 1) consecutive ones).  48 stations, 1024 channels: 37.4 us with one thread per
+// input walking its row and its column, 19.2 us in this form (77 MB read: 12.5 us at the copy rate).
+__global__ __launch_bounds__(512) void apply_gains_adjoint_kernel(const float2* __restrict__ vis0, const float2* __restrict__ gains,
                                                                   const float2* __restrict__ grad_vis, float2* __restrict__ grad_gains,
-                                                                  int S, int M) {
-    const int k = threadIdx.x;
-    if (k >= M) return;
+                                                                  int S) {
+    __shared__ float2 part[kMaxStations][8][2];    // row sums [s1][wave][p1]
+    __shared__ float2 col[4 * kMaxStations];       // column sums [thread]
+    const int j = threadIdx.x, wave = j >> 6, n_wave = blockDim.x >> 6;
+    const int s2 = j >> 2, p1 = (j >> 1) & 1, p2 = j & 1;
     const int64_t ch = blockIdx.x;
-    const int64_t B = (int64_t)S * (S + 1) / 2;
-    const float2* v0 = vis0 + ch * B * 4;
-    const float2* G = grad_vis + ch * B * 4;
-    const float2* g = gains + ch * M;
-    const int sk = k >> 1, pk = k & 1;
+    const int64_t n4 = (int64_t)S * (S + 1) * 2;   // entries of a channel
+    const float2* v0 = vis0 + ch * n4 + j;
+    const float2* G = grad_vis + ch * n4 + j;
+    const float2* g = gains + ch * 2 * S;
+    const float2 gb = s2 < S ? g[2 * s2 + p2] : make_float2(0.f, 0.f);
     float2 acc = make_float2(0.f, 0.f);
-    // entries with a = k: baselines (sk, s2), s2 <= sk, pol pair (pk, p2)
-    for (int s2 = 0; s2 <= sk; ++s2) {
-        const int64_t base = ((int64_t)sk * (sk + 1) / 2 + s2) * 4 + 2 * pk;
+    // rows below this wave's first station hold no entry of its threads
+    constexpr int kU = 8;                          // rows in flight
+    for (int r0 = 16 * wave; r0 < S; r0 += kU) {
+        float2 v[kU], w[kU], ga[kU];
 #pragma unroll
-        for (int p2 = 0; p2 < 2; ++p2) {
-            const float2 t = cmul(cmul(G[base + p2], g[2 * s2 + p2]), cconj(v0[base + p2]));
-            acc.x += t.x;
-            acc.y += t.y;
+        for (int u = 0; u < kU; ++u) {
+            const int s1 = r0 + u;
+            const bool ok = s1 < S && s2 <= s1;
+            const int at = 2 * s1 * (s1 + 1);
+            v[u] = ok ? v0[at] : make_float2(0.f, 0.f);
+            w[u] = ok ? G[at] : make_float2(0.f, 0.f);
+            ga[u] = ok ? g[2 * s1 + p1] : make_float2(0.f, 0.f);
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int s1 = r0 + u;
+            if (s1 >= S) break;
+            const bool ok = s2 <= s1;
+            const float2 P = cmul(w[u], cconj(v[u]));
+            const float2 t = cmul(cconj(P), ga[u]), rsum = cmul(P, gb);
+            acc.x += ok ? t.x : 0.f;
+            acc.y += ok ? t.y : 0.f;
+            const float x = add_same_p1(ok ? rsum.x : 0.f), y = add_same_p1(ok ? rsum.y : 0.f);
+            if ((j & 63) == 2 * p1) part[s1][wave][p1] = make_float2(x, y);
         }
     }
-    // entries with b = k: baselines (s1, sk), s1 >= sk, pol pair (p1, pk)
-    for (int s1 = sk; s1 < S; ++s1) {
-        const int64_t base = ((int64_t)s1 * (s1 + 1) / 2 + sk) * 4 + pk;
-#pragma unroll
-        for (int p1 = 0; p1 < 2; ++p1) {
-            const float2 t = cmul(cmul(cconj(G[base + 2 * p1]), g[2 * s1 + p1]), v0[base + 2 * p1]);
-            acc.x += t.x;
-            acc.y += t.y;
-        }
+    col[j] = acc;
+    __syncthreads();
+    if (j >= 2 * S) return;
+    // input j = (station, pol): its row sums over the waves that hold entries of the row, then its
+    // column sums over p1
+    const int s = j >> 1, p = j & 1;
+    float2 r = make_float2(0.f, 0.f);
+    for (int w = 0; w < n_wave && 16 * w <= s; ++w) {
+        r.x += part[s][w][p].x;
+        r.y += part[s][w][p].y;
     }
-    grad_gains[ch * M + k] = acc;
+    const float2 c0 = col[4 * s + p], c1 = col[4 * s + 2 + p];
+    grad_gains[ch * 2 * S + j] = make_float2(r.x + (c0.x + c1.x), r.y + (c0.y + c1.y));
 }
 
 }  // namespace
 
 hipError_t launch_apply_gains(const void* vis0, const void* gains, void* vis, int n_chan, int S, hipStream_t st) {
-    const int64_t B = (int64_t)S * (S + 1) / 2;
-    const int64_t n = (int64_t)n_chan * B * 4;
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(apply_gains_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (const float2*)vis0,
-                       (const float2*)gains, (float2*)vis, n, (int)B, 2 * S);
+    const int B = S * (S + 1) / 2, per_ch = (2 * B + 255) / 256;
+    if (n_chan == 0) return hipSuccess;
+    hipLaunchKernelGGL(apply_gains_kernel, dim3((unsigned)((int64_t)n_chan * per_ch)), dim3(256), 0, st, (const float4*)vis0,
+                       (const float2*)gains, (float4*)vis, B, 2 * S, per_ch);
     return hipGetLastError();
 }
 
 hipError_t launch_apply_gains_adjoint(const void* vis0, const void* gains, const void* grad_vis, void* grad_gains, int n_chan,
                                       int S, hipStream_t st) {
     if (n_chan == 0) return hipSuccess;
-    hipLaunchKernelGGL(apply_gains_adjoint_kernel, dim3((unsigned)n_chan), dim3(256), 0, st, (const float2*)vis0,
-                       (const float2*)gains, (const float2*)grad_vis, (float2*)grad_gains, S, 2 * S);
+    hipLaunchKernelGGL(apply_gains_adjoint_kernel, dim3((unsigned)n_chan), dim3((unsigned)((4 * S + 63) / 64 * 64)), 0, st,
+                       (const float2*)vis0, (const float2*)gains, (const float2*)grad_vis, (float2*)grad_gains, S);
     return hipGetLastError();
 }
 
