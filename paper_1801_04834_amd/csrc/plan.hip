@@ -852,10 +852,16 @@ int cobalt_correlate_noalloc(const cobalt_config* cfg, const void* d_in, const d
                                                                : 1.0;
     for (int c = 0; c < z.C; ++c) bscale[c] = (float)((cfg->h_bandpass ? (double)cfg->h_bandpass[c] : 1.0) * mode_scale);
     // the tables travel in kernel arguments: nothing of the caller's is read after the call, also
-    // when the call is captured into a graph
-    hipError_t e = launch_upload(base + o_fir, cfg->h_fir, sizeof(float) * kT * z.C, st);
-    if (e == hipSuccess) e = launch_upload(base + o_bsc, bscale, sizeof(float) * z.C, st);
-    if (e == hipSuccess) e = launch_upload(base + o_fsb, cfg->h_subband_freq_hz, sizeof(double) * z.SB, st);
+    // when the call is captured into a graph.  They are neighbours in the scratch array, so all of
+    // them go up together (up to 256 subbands; more frequencies follow in uploads of their own).
+    char tab[kT * 256 * 4 + 256 * 4 + 256 * 8];
+    const int64_t n_f = z.SB < 256 ? z.SB : 256;
+    std::memcpy(tab, cfg->h_fir, sizeof(float) * kT * z.C);
+    std::memcpy(tab + (o_bsc - o_fir), bscale, sizeof(float) * z.C);
+    std::memcpy(tab + (o_fsb - o_fir), cfg->h_subband_freq_hz, sizeof(double) * n_f);
+    hipError_t e = launch_upload(base + o_fir, tab, o_fsb - o_fir + (int64_t)sizeof(double) * n_f, st);
+    if (e == hipSuccess && z.SB > n_f)
+        e = launch_upload(base + o_fsb + sizeof(double) * n_f, cfg->h_subband_freq_hz + n_f, (int64_t)sizeof(double) * (z.SB - n_f), st);
     if (e != hipSuccess) return hip_fail(e, "table upload");
     if (!d_hist_in) {
         e = launch_zero_fill(base + o_hzero, hist, st);      // a fill kernel, no memset node

@@ -478,7 +478,8 @@ hipError_t launch_mode(const XArgs& a, hipStream_t st) {
 // n_tg wave groups in each and TPW tiles per wave; the 8 / n_tg waves of a group split the k-steps
 // among them (8 samples each) and add their sums through LDS at the end, in a fixed order.  A
 // 16-byte fragment of lane i (row i % 16, samples 2 (i / 16) and 2 (i / 16) + 1 of a k-step) is
-// four k values of an A and of a B operand; Im takes (-im, re) as B.
+// four k values of an A and of a B operand; Im takes (-im, re) as B.  On a diagonal tile the two
+// products of Im are each other's negative transposes, so only Q = im re^T is formed and Im = Q - Q^T.
 // Bound by the FP32 matrix pipes (a library product reaches 154 TFLOP/s here).  Tiles of 16 waste
 // less of the triangle than tiles of 32 (24 stations: 6 x 256 against 3 x 1024 products per k), and
 // the k-split keeps all eight waves busy at any station count.  Against complex FMAs on the vector
@@ -541,13 +542,15 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void xstage_f32_kernel(XArgs a, 
                     const floatx4 A = *(const floatx4*)(base + ti[t] * (16 * kRowB));
                     const floatx4 B = *(const floatx4*)(base + tj[t] * (16 * kRowB));
                     re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[0], B[0], re[t], 0, 0, 0);
-                    im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[0], -B[1], im[t], 0, 0, 0);
-                    re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[1], B[1], re[t], 0, 0, 0);
                     im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[1], B[0], im[t], 0, 0, 0);
-                    re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[2], B[2], re[t], 0, 0, 0);
-                    im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[2], -B[3], im[t], 0, 0, 0);
-                    re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[3], B[3], re[t], 0, 0, 0);
+                    re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[1], B[1], re[t], 0, 0, 0);
                     im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[3], B[2], im[t], 0, 0, 0);
+                    re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[2], B[2], re[t], 0, 0, 0);
+                    re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[3], B[3], re[t], 0, 0, 0);
+                    if (ti[t] != tj[t]) {
+                        im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[0], -B[1], im[t], 0, 0, 0);
+                        im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[2], -B[3], im[t], 0, 0, 0);
+                    }
                 }
                 if (++since == kF32Fold) {
                     since = 0;
@@ -590,9 +593,17 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void xstage_f32_kernel(XArgs a, 
     }
     if (kpart != 0) return;
     const int64_t B = (int64_t)a.S * (a.S + 1) / 2;
+    float* tr = (float*)lds + tg * (16 * 17);
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
         const int b = 16 * tj[t] + (lane & 15);
+        if (ti[t] == tj[t]) {
+            // the same wave reads its transpose back (its LDS operations complete in order)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tr[(4 * (lane >> 4) + r) * 17 + (lane & 15)] = tim[t][r];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tim[t][r] -= tr[(lane & 15) * 17 + 4 * (lane >> 4) + r];
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int aa = 16 * ti[t] + 4 * (lane >> 4) + r;
