@@ -537,10 +537,17 @@ __global__ __launch_bounds__(64 * kF32Waves, 2) void xstage_f32_kernel(XArgs a, 
             for (step = kpart; step < 4 * nch; step += n_kp) {
                 const char* base = buf + (step >> 2) * q.chunk_b + (lane & 15) * kRowB +
                                    (((4 * (step & 3) + (lane >> 4)) ^ (lane & 15)) << 4);
+                // each tile's fragments are read before the products of the tile before it
+                floatx4 An = *(const floatx4*)(base + ti[0] * (16 * kRowB));
+                floatx4 Bn = *(const floatx4*)(base + tj[0] * (16 * kRowB));
 #pragma unroll
                 for (int t = 0; t < TPW; ++t) {
-                    const floatx4 A = *(const floatx4*)(base + ti[t] * (16 * kRowB));
-                    const floatx4 B = *(const floatx4*)(base + tj[t] * (16 * kRowB));
+                    const floatx4 A = An, B = Bn;
+                    if (t + 1 < TPW) {
+                        An = *(const floatx4*)(base + ti[t + 1] * (16 * kRowB));
+                        Bn = *(const floatx4*)(base + tj[t + 1] * (16 * kRowB));
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                     re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[0], B[0], re[t], 0, 0, 0);
                     im[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[1], B[0], im[t], 0, 0, 0);
                     re[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(A[1], B[1], re[t], 0, 0, 0);
