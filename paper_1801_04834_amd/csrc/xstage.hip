@@ -637,12 +637,15 @@ hipError_t launch_xstage_fp32(const XArgs& a, hipStream_t st) {
     XF32 f{};
     f.nb = (a.M + 15) / 16;
     f.n_tiles = f.nb * (f.nb + 1) / 2;
-    // Split with the least time per CU: rounds of workgroups x tile slots per channel share.  A
-    // smaller number of workgroups per channel reads the channel fewer times; fewer wave groups
-    // waste fewer slots but need the k-split sums, so ties go to more groups of waves.
+    // Split with the least time per CU: rounds of workgroups x tile slots per channel share.  Every
+    // workgroup of a channel reads all of it, so there are several only where their tiles need them
+    // (more than 8 x 9 tiles) or CUs would idle otherwise (40 stations, 512 channels: three workgroups
+    // waste no slot and take 690 us, one takes 480); ties go to fewer groups of waves, whose waves
+    // hold more tiles per barrier (40 stations: 478 us with two groups, 517 with eight).
     int best = 0x7fffffff, tpw = 1;
-    for (int groups = 1; groups <= 4; ++groups)
-        for (int n_tg = kF32Waves; n_tg >= 1; n_tg /= 2) {
+    const int least = (f.n_tiles + kF32Waves * kF32MaxTpw - 1) / (kF32Waves * kF32MaxTpw);
+    for (int groups = least; groups <= 4 && (groups == least || (int64_t)a.n_chan * groups <= kCUs); ++groups)
+        for (int n_tg = 1; n_tg <= kF32Waves; n_tg *= 2) {
             const int per = (f.n_tiles + groups * n_tg - 1) / (groups * n_tg);
             if (per > kF32MaxTpw) continue;
             const int64_t rounds = ((int64_t)a.n_chan * groups + kCUs - 1) / kCUs;
