@@ -20,7 +20,10 @@
 //   Delay: per (channel, sample) the phase in cycles f_c * tau(j) is formed with one FP64
 //          FMA and reduced with FP64 rint; the reduced phase is rotated in FP32 with the
 //          hardware sin/cos (argument in revolutions).
-//   Store: lanes with equal h write 32 consecutive channel samples of one channel row.
+//   Store: the 32 lanes of one h write 32 consecutive channel samples of one channel row; h is the
+//          lane's upper bit, so that a quarter wave writes whole 64-byte pieces (with h the lowest
+//          bit the two rows interleaved: 24 stations x 32 subbands 785 -> 768 us, 256 channels, 24 x 8
+//          244 -> 232, 48 x 61 3361 -> 3273).
 #include <cstring>
 
 #include "cobalt_internal.h"
@@ -30,10 +33,11 @@ namespace {
 
 constexpr int kPass = 32;                 // channel samples per pass (= one K block)
 static_assert(kPass == kKBlock, "a pass writes exactly one K block per channel");
-constexpr int kRowF2 = 68;                // complex staging row (float2): two 32-point halves, 16 B apart
-constexpr int kHalfF2 = 34;
-constexpr int kRowF1 = 72;                // split staging row (floats): conflict-free 16-byte column reads
-constexpr int kHalfF1 = 36;
+// Staging rows of two 32-point halves: 4 banks beyond a multiple of 64, so that the 16-byte reads of
+// 16 rows by 16 lanes cover all banks
+constexpr int kRowF2 = 66;                // complex staging row (float2)
+constexpr int kRowF1 = 68;                // split staging row (floats)
+constexpr int kHalf = 32;
 
 constexpr double kPi = 3.141592653589793238462643383279502884;
 
@@ -231,8 +235,18 @@ __global__ __launch_bounds__(C) __attribute__((amdgpu_waves_per_eu(fstage_waves<
     float* const ylds = lds_f + wv * kYl;
     // grid order: input row fastest, so neighbouring rows of one channel K block are
     // written by concurrently running waves (contiguous in the K-blocked layout)
-    const int row_in = (int)(blockIdx.x % (unsigned)a.M);               // input index s*P + p
-    const int rest = (int)(blockIdx.x / (unsigned)a.M);
+    // Blocks are dealt to the 8 XCDs in turn: of every 8 kRun consecutive ones each XCD takes kRun
+    // consecutive rows, so that the 128-byte lines of a K block that leave one XCD's L2 together are
+    // neighbours (76 stations, 16 subbands: 1241 -> 1215 us; 37 x 11 ragged 239 -> 223; 60 x 8 cf32
+    // 614 -> 608).  Int8 output, 64 bytes per row, gains nothing (942 -> 950) and keeps the plain order.
+    constexpr unsigned kRun = 8;
+    unsigned bid = blockIdx.x;
+    if (OM != XM_INT8 && (bid / (8 * kRun) + 1) * (8 * kRun) <= gridDim.x) {
+        const unsigned r = bid % (8 * kRun);
+        bid = bid - r + (r % 8) * kRun + r / 8;
+    }
+    const int row_in = (int)(bid % (unsigned)a.M);                      // input index s*P + p
+    const int rest = (int)(bid / (unsigned)a.M);
     const int chunk = rest % a.n_chunks;
     const int sb = rest / a.n_chunks;
     const int64_t st = (int64_t)row_in * a.SB + sb;                      // input stream (s*P + p)*SB + sb
@@ -276,7 +290,7 @@ __global__ __launch_bounds__(C) __attribute__((amdgpu_waves_per_eu(fstage_waves<
 
     const double tau0 = a.delays[2 * s], tau1 = a.delays[2 * s + 1];
     const double fsb = a.f_sb[sb];
-    const int jj = lane >> 1, hh = lane & 1;
+    const int jj = lane & 31, hh = lane >> 5;
 
     const int j0 = chunk * a.chunk;
     const int jend = min(j0 + a.chunk, a.pitch);
@@ -386,11 +400,11 @@ __global__ __launch_bounds__(C) __attribute__((amdgpu_waves_per_eu(fstage_waves<
                 const float dr = r0r - r1r, di = r0i - r1i;
                 const int row = 2 * pr + (lane >> 5), q = lane & 31;
                 yl[row * kRowF2 + q] = make_float2(r0r + r1r, r0i + r1i);
-                yl[row * kRowF2 + kHalfF2 + q] = make_float2(dr * wcs + di * wsn, di * wcs - dr * wsn);
+                yl[row * kRowF2 + kHalf + q] = make_float2(dr * wcs + di * wsn, di * wcs - dr * wsn);
             }
             __syncthreads();
             // ---- 32-point DFT of the even (h = 0) or odd (h = 1) output bins ----
-            const float2* src = &yl[jj * kRowF2 + hh * kHalfF2];
+            const float2* src = &yl[jj * kRowF2 + hh * kHalf];
 #pragma unroll
             for (int q = 0; q < 32; ++q) {
                 const float2 v = src[q];
@@ -411,14 +425,13 @@ __global__ __launch_bounds__(C) __attribute__((amdgpu_waves_per_eu(fstage_waves<
                 const float dr = r0r - r1r, di = r0i - r1i;
                 const int row = 2 * pr + (lane >> 5), q = lane & 31;
                 ylds[row * kRowF1 + q] = r0r + r1r;
-                ylds[row * kRowF1 + kHalfF1 + q] = dr * wcs + di * wsn;
+                ylds[row * kRowF1 + kHalf + q] = dr * wcs + di * wsn;
                 im_hold[2 * pr] = r0i + r1i;
                 im_hold[2 * pr + 1] = di * wcs - dr * wsn;
             }
             __syncthreads();
-            // lane (jj, hh) reads row jj, half hh: with rows of 72 floats and halves 36 apart,
-            // any 16 lanes' 16-byte reads cover 64 distinct banks
-            const float* src = &ylds[jj * kRowF1 + hh * kHalfF1];
+            // lane (jj, hh) reads row jj, half hh
+            const float* src = &ylds[jj * kRowF1 + hh * kHalf];
 #pragma unroll
             for (int q = 0; q < 32; ++q) xr[q] = src[q];
             __syncthreads();
@@ -426,7 +439,7 @@ __global__ __launch_bounds__(C) __attribute__((amdgpu_waves_per_eu(fstage_waves<
             for (int pr = 0; pr < kPass / 2; ++pr) {
                 const int row = 2 * pr + (lane >> 5), q = lane & 31;
                 ylds[row * kRowF1 + q] = im_hold[2 * pr];
-                ylds[row * kRowF1 + kHalfF1 + q] = im_hold[2 * pr + 1];
+                ylds[row * kRowF1 + kHalf + q] = im_hold[2 * pr + 1];
             }
             __syncthreads();
 #pragma unroll
