@@ -224,8 +224,13 @@ def device_copy(dst, src, stream=None):
 
 
 def _stream_handle(torch, stream, device):
-    s = stream if stream is not None else torch.cuda.current_stream(device)
-    return ct.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return ct.c_void_p(stream.cuda_stream)
+    # the handle itself, without building a Stream object around it (0.5 us instead of 4 on every call)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or device.index is None:
+        return ct.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    return ct.c_void_p(raw(device.index))
 
 
 class Plan:
@@ -304,7 +309,7 @@ class Plan:
 
     # ---- calls -----------------------------------------------------------------------
     def _dev(self, t, shape, dtype, name):
-        if t.device != self.device or t.dtype != dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous():
+        if t.dtype != dtype or t.shape != shape or t.device != self.device or not t.is_contiguous():
             raise ValueError(f"{name}: need contiguous {dtype} {tuple(shape)} on {self.device}, "
                              f"got {t.dtype} {tuple(t.shape)} on {t.device}")
         return ct.c_void_p(t.data_ptr())
@@ -529,7 +534,7 @@ def correlate_noalloc(x, delays, out, hist_in=None, hist_out=None, stream=None, 
     def chk(t, shape, dt, name):
         if t is None:
             return None
-        if not t.is_cuda or t.dtype != dt or tuple(t.shape) != tuple(shape) or not t.is_contiguous():
+        if not t.is_cuda or t.dtype != dt or t.shape != shape or not t.is_contiguous():
             raise ValueError(f"{name}: need contiguous {dt} {tuple(shape)} on the GPU, got {t.dtype} {tuple(t.shape)}")
         return ct.c_void_p(t.data_ptr())
 
