@@ -140,12 +140,15 @@ template <> struct Samp<ST_CF32> {
     static __device__ __forceinline__ float2 cvt(raw_t w) { return w; }
 };
 
-// One pass of input rows (32 rows x this lane's phase).  8-bit samples are packed two
-// rows per VGPR (16-bit halves), wider samples take one element per row.
+// One pass of input rows (32 rows x this lane's phase) and the 15 rows before it.  at(w) converts
+// window row w (0 .. 46: the rows before the pass, then its own).  8-bit samples are kept two rows
+// per register, (re, im) of an even row in the low half, and converted straight from their byte: the
+// packing costs one instruction per two rows, and the rows before the pass are the last eight words
+// of the pass before (16-bit halves in registers of their own took ~140 more instructions per pass).
 template <int ST, int C>
 struct PassBuf {
     using raw_t = typename Samp<ST>::raw_t;
-    raw_t v[kPass];
+    raw_t v[kPass], tail[kHistRows];
     // rows jb .. jb + 31 of this wave's phases: a wave-uniform base for the pass and per-lane
     // offsets lane + r*C, so the loads take a scalar base, one offset register and immediates
     __device__ __forceinline__ void load(const raw_t* __restrict__ in, int lane, int jb, int n_c) {
@@ -158,27 +161,47 @@ struct PassBuf {
             for (int r = 0; r < kPass; ++r) v[r] = jb + r < n_c ? rows[r * C + lane] : raw_t{};
         }
     }
-    __device__ __forceinline__ raw_t get(int r) const { return v[r]; }
+    __device__ __forceinline__ void set_tail(int i, raw_t x) { tail[i] = x; }
+    __device__ __forceinline__ void keep_tail() {
+#pragma unroll
+        for (int i = 0; i < kHistRows; ++i) tail[i] = v[kPass - kHistRows + i];
+    }
+    __device__ __forceinline__ float2 at(int w) const { return Samp<ST>::cvt(w < kHistRows ? tail[w] : v[w - kHistRows]); }
 };
-typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 template <int C>
 struct PassBuf<ST_CI8, C> {
-    ushort2v v[kPass / 2];
+    uint32_t v[kPass / 2], tail[(kHistRows + 1) / 2];   // tail word i: rows 2i - 16 and 2i - 15 before the pass
     __device__ __forceinline__ void load(const uint16_t* __restrict__ in, int lane, int jb, int n_c) {
         const uint16_t* __restrict__ rows = in + (int64_t)jb * C;
         if (jb + kPass <= n_c) {
 #pragma unroll
-            for (int r = 0; r < kPass; ++r) v[r / 2][r % 2] = rows[r * C + lane];
+            for (int r = 0; r < kPass; r += 2) v[r / 2] = rows[r * C + lane] | (uint32_t)rows[(r + 1) * C + lane] << 16;
         } else {
 #pragma unroll
-            for (int r = 0; r < kPass; ++r) v[r / 2][r % 2] = jb + r < n_c ? rows[r * C + lane] : (uint16_t)0;
+            for (int r = 0; r < kPass; r += 2)
+                v[r / 2] = (jb + r < n_c ? rows[r * C + lane] : 0u) | (jb + r + 1 < n_c ? (uint32_t)rows[(r + 1) * C + lane] : 0u) << 16;
         }
     }
-    __device__ __forceinline__ uint16_t get(int r) const { return v[r / 2][r % 2]; }
+    // row i - 15 before the pass, i ascending from 0
+    __device__ __forceinline__ void set_tail(int i, uint16_t x) {
+        if (i % 2 == 0) tail[(i + 1) / 2] = (i == 0 ? 0u : tail[(i + 1) / 2]) | (uint32_t)x << 16;
+        else tail[(i + 1) / 2] = x;
+    }
+    __device__ __forceinline__ void keep_tail() {
+#pragma unroll
+        for (int i = 0; i < (kHistRows + 1) / 2; ++i) tail[i] = v[kPass / 2 - (kHistRows + 1) / 2 + i];
+    }
+    __device__ __forceinline__ float2 at(int w) const {
+        const uint32_t x = w < kHistRows ? tail[(w + 1) / 2] : v[(w - kHistRows) / 2];
+        const bool odd = w < kHistRows ? w % 2 == 0 : (w - kHistRows) % 2 != 0;   // in the high half
+        return odd ? make_float2((float)(int8_t)(x >> 16), (float)((int32_t)x >> 24))
+                   : make_float2((float)(int8_t)x, (float)(int8_t)(x >> 8));
+    }
 };
 
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef float float2v __attribute__((ext_vector_type(2)));
+typedef unsigned uint2v __attribute__((ext_vector_type(2)));
 
 template <int OM> struct OutFmt;
 template <> struct OutFmt<XM_FP32> { static constexpr int kPlanes = 1, kElem = 8; };
@@ -267,6 +290,11 @@ __global__ __launch_bounds__(C) __attribute__((amdgpu_waves_per_eu(fstage_waves<
     const uint32_t pstride = (uint32_t)(a.M * kKBlock * O_::kElem);                          // bytes between planes
     const uint32_t kbstride = (uint32_t)(O_::kPlanes * a.M * kKBlock * O_::kElem);           // bytes between K blocks
     const uint32_t ulane = (uint32_t)lane;
+    // one subband's channelised data stay below 2 GiB: buffer stores with the channel in the scalar
+    // offset cost no address arithmetic per lane (the two planes of FP16-split output store as fast
+    // through a scalar and a vector base: 24 stations x 32 subbands 797 us against 805)
+    const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc((void*)out, (short)0, 0x7fffffff, 0x00020000);
+    constexpr int kNt = 2;                                                                   // non-temporal
 
     // The last chunk of every stream writes the history for the next block: the final
     // (T-1)*C samples of [old history, block].
@@ -295,15 +323,15 @@ __global__ __launch_bounds__(C) __attribute__((amdgpu_waves_per_eu(fstage_waves<
     const int j0 = chunk * a.chunk;
     const int jend = min(j0 + a.chunk, a.pitch);
 
-    raw_t tail[kHistRows];                     // raw samples of the 15 rows before the pass
-    if (j0 >= kHistRows && j0 <= a.n_c) {
+    PassBuf<ST, C> nw;
+    if (j0 >= kHistRows && j0 <= a.n_c) {      // the 15 rows before the pass
 #pragma unroll
-        for (int i = 0; i < kHistRows; ++i) tail[i] = inw[(uint32_t)((j0 - kHistRows + i) * C) + ulane];
+        for (int i = 0; i < kHistRows; ++i) nw.set_tail(i, inw[(uint32_t)((j0 - kHistRows + i) * C) + ulane]);
     } else {
 #pragma unroll
         for (int i = 0; i < kHistRows; ++i) {
             const int r = j0 - kHistRows + i;  // wave-uniform
-            tail[i] = r < 0 ? holdw[(r + kHistRows) * C + lane] : r < a.n_c ? inw[r * C + lane] : raw_t{};
+            nw.set_tail(i, r < 0 ? holdw[(r + kHistRows) * C + lane] : r < a.n_c ? inw[r * C + lane] : raw_t{});
         }
     }
 
@@ -311,31 +339,28 @@ __global__ __launch_bounds__(C) __attribute__((amdgpu_waves_per_eu(fstage_waves<
     // so their HBM latency overlaps the FFT, delay and store work of this pass (8/16-bit
     // samples; float samples, 2 VGPRs each, are loaded at the top of the pass instead).
     constexpr bool kPrefetch = ST != ST_CF32;
-    PassBuf<ST, C> nw;
     if constexpr (kPrefetch) nw.load(inw, lane, j0, a.n_c);
 
     for (int jb = j0; jb < jend; jb += kPass) {
         if constexpr (!kPrefetch) nw.load(inw, lane, jb, a.n_c);
 
         // ---- polyphase FIR: y_j[p] = sum_t h[t*C + p] x[(j - T + 1 + t)*C + p] ----
-        // input-stationary: window row w feeds outputs j = w - t (taps in ascending t)
+        // input-stationary: window row w feeds outputs j = w - t (taps in ascending t; the first
+        // product starts the sum, so there is nothing to clear)
         float2 acc[kPass];
 #pragma unroll
-        for (int j = 0; j < kPass; ++j) acc[j] = make_float2(0.f, 0.f);
-#pragma unroll
         for (int w = 0; w < kPass + kHistRows; ++w) {
-            const float2 x = S_::cvt(w < kHistRows ? tail[w] : nw.get(w - kHistRows));
+            const float2 x = nw.at(w);
 #pragma unroll
             for (int t = 0; t < kT; ++t) {
                 const int j = w - t;
                 if (j >= 0 && j < kPass) {
-                    acc[j].x = fmaf(h[t], x.x, acc[j].x);
-                    acc[j].y = fmaf(h[t], x.y, acc[j].y);
+                    acc[j].x = t == 0 ? h[t] * x.x : fmaf(h[t], x.x, acc[j].x);
+                    acc[j].y = t == 0 ? h[t] * x.y : fmaf(h[t], x.y, acc[j].y);
                 }
             }
         }
-#pragma unroll
-        for (int i = 0; i < kHistRows; ++i) tail[i] = nw.get(kPass - kHistRows + i);
+        nw.keep_tail();
         if constexpr (kPrefetch) {
             if (jb + kPass < jend) nw.load(inw, lane, jb + kPass, a.n_c);
         }
@@ -466,24 +491,27 @@ __global__ __launch_bounds__(C) __attribute__((amdgpu_waves_per_eu(fstage_waves<
             if (q % 4 == 0) {
                 ph = phasor_rev(fma((double)(2 * kW * q), c1, c0));
             } else {
-                const float pr_ = ph.x * step.x - ph.y * step.y;
-                ph.y = ph.x * step.y + ph.y * step.x;
+                // the fused products are spelt out: left to the compiler, their choice moves with the code
+                // around them, and the last bit with it (requantised samples have to stay the same; 16-bit
+                // input at 64 channels has always fused the other product)
+                const float pr_ = fmaf(step.x, ph.x, -(ph.y * step.y));
+                if constexpr (ST == ST_CI16 && C == 64) ph.y = fmaf(step.y, ph.x, ph.y * step.x);
+                else ph.y = fmaf(step.x, ph.y, ph.x * step.y);
                 ph.x = pr_;
             }
             const int m = (q + 16) & 31;               // FFT bin 2m + hh is channel 2q + hh
             const int i = bitrev5(m);                  // register holding bin m
             const float b = blds[2 * kW * q + kW * hh + wv];   // bandpass x mode scale of channel c
             const float pr_ = ph.x * b, pi_ = ph.y * b;
-            const float zr = xr[i] * pr_ - xi[i] * pi_;
-            const float zi = xr[i] * pi_ + xi[i] * pr_;
-            // the channel's base is wave-uniform (scalar adds); lane offsets are loop-invariant
-            char* outq = out + (size_t)((uint32_t)(2 * kW * q) * cstride);
-            char* dst = outq + lane_off;
+            const float zr = fmaf(xr[i], pr_, -(xi[i] * pi_));
+            const float zi = fmaf(xr[i], pi_, xi[i] * pr_);
+            // the channel's offset is wave-uniform (scalar adds); lane offsets are loop-invariant
+            const uint32_t qoff = (uint32_t)(2 * kW * q) * cstride;
             // non-temporal stores: the channelised data is written once here and read once by
             // the next kernel (measured 1-2 % faster than cached stores)
             if constexpr (OM == XM_FP32) {
-                const float2v z2 = {zr, zi};
-                __builtin_nontemporal_store(z2, (float2v*)dst);
+                const uint2v z2 = {__float_as_uint(zr), __float_as_uint(zi)};
+                __builtin_amdgcn_raw_buffer_store_b64(z2, orsrc, (int)lane_off, (int)qoff, kNt);
             } else if constexpr (OM == XM_FP16_SPLIT) {
                 // hi = fp16(z) (round to nearest even), lo = fp16(z - hi).  z - hi is exact in
                 // FP32, so v_fma_mix{lo,hi}_f16 (z + 1 * (-hi) with hi read as fp16, result
@@ -504,13 +532,17 @@ __global__ __launch_bounds__(C) __attribute__((amdgpu_waves_per_eu(fstage_waves<
                 unsigned lb;
                 asm("v_fma_mixlo_f16 %0, %1, 1.0, -%2 op_sel_hi:[0,0,1]" : "=v"(lb) : "v"(zr_), "v"(hb));
                 asm("v_fma_mixhi_f16 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lb) : "v"(zi_), "v"(hb));
-                __builtin_nontemporal_store(hb, (unsigned*)dst);
+                char* outq = out + (size_t)qoff;
+                __builtin_nontemporal_store(hb, (unsigned*)(outq + lane_off));
                 __builtin_nontemporal_store(lb, (unsigned*)(outq + lane_off_lo));
             } else {
-                const float qr = fminf(fmaxf(rintf(zr), -127.f), 127.f);
-                const float qi = fminf(fmaxf(rintf(zi), -127.f), 127.f);
-                const unsigned short v = (unsigned short)(((unsigned)(int)qr & 0xffu) | (((unsigned)(int)qi & 0xffu) << 8));
-                __builtin_nontemporal_store(v, (unsigned short*)dst);
+                // clamp(rint(z), +-127) = rint(clamp(z, +-127)); adding 1.5 x 2^23 rounds to nearest even
+                // and leaves the integer in the low mantissa bits (one median and one addition per
+                // component and one byte permute, instead of eleven instructions)
+                const float qr = __builtin_amdgcn_fmed3f(zr, -127.f, 127.f) + 12582912.f;
+                const float qi = __builtin_amdgcn_fmed3f(zi, -127.f, 127.f) + 12582912.f;
+                const unsigned short v = (unsigned short)__builtin_amdgcn_perm(__float_as_uint(qi), __float_as_uint(qr), 0x0c0c0400u);
+                __builtin_amdgcn_raw_buffer_store_b16(v, orsrc, (int)lane_off, (int)qoff, kNt);
             }
             if (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // bound live ranges per 4 channels
         }
