@@ -236,7 +236,7 @@ template <int MODE, int NB, int NWV, int G> constexpr int ks_tiles() {
     const int left = tile_count(NB) - G * ks_per<MODE, NB, NWV>();
     return left < ks_per<MODE, NB, NWV>() ? left : ks_per<MODE, NB, NWV>();
 }
-template <int NB, int NWV> constexpr int ks_lds() { return NWV == 8 ? 147456 : NB <= 2 ? 40960 : NB == 3 ? 53248 : 81920; }
+template <int NB, int NWV> constexpr int ks_lds() { return NWV == 8 ? 163840 : NB <= 2 ? 40960 : NB == 3 ? 53248 : 81920; }
 template <int NB, int NWV> constexpr int ks_waves_per_simd() { return NWV == 8 ? 2 : NB <= 2 ? 4 : NB == 3 ? 3 : 2; }
 // row blocks used by tiles [t0, t0 + n)
 constexpr unsigned ks_blocks(int NB, int t0, int n) {
