@@ -29,7 +29,7 @@ METRIC = "correlator TeraMACs/s and real-time factor at 76 stations; p99 block l
 HBM_PEAK_GBS = 8000.0
 FP16_MFMA_PEAK_TFLOPS = 2516.6       # dense fp16 MFMA, 256 CU x 2.4 GHz x 4096 flop/clk
 INT8_MFMA_PEAK_TOPS = 5033.2
-FP32_VALU_PEAK_TFLOPS = 157.3        # published vector FP32 (dual-issue/packed)
+FP32_MFMA_PEAK_TFLOPS = 157.3        # published matrix FP32
 # FP32 vector FMA without packed math (these kernels are built with packed FP32 disabled):
 # 256 CU x 4 SIMD x 16 lanes x 2 flop x 2.4 GHz
 FP32_VALU_NOPACK_TFLOPS = 78.6
@@ -67,6 +67,11 @@ def measured_traffic(kernel):
 
 KERNEL_SOURCES = (("fstage_kernel", "fstage.hip"), ("xstage_", "xstage.hip"), ("beam_transform_kernel", "beamxf.hip"),
                   ("beam_kernel", "beam.hip"))
+
+
+def x_kernel_name(w):
+    """The X stage's instantiation at the benchmark's sizes (more channels than compute units)."""
+    return "xstage_f32_kernel" if w.x_mode == 0 else f"xstage_ksplit_kernel<{w.x_mode}, {(w.M + 15) // 16}, 4>"
 
 
 def write_traffic(fetch_dir, write_dir, bench_json, copy_mib=1024):
@@ -411,7 +416,7 @@ def int8_leg(args, torch, binding, synth, dev, probe):
     f_tf = samples * F_FLOP_PER_SAMPLE / f_s / 1e12
     x_tops = cmacs * 8 / x_s / 1e12
     f_kernel = f"fstage_kernel<{w.sample_type}, {w.x_mode}, {w.C}>"
-    x_kernel = f"xstage_mfma_kernel<{w.x_mode}, {(w.M + 31) // 32}>"
+    x_kernel = x_kernel_name(w)
     out = {
         "workload": f"int8_full: {w.S} stations x 2 pol, {w.SB} subbands, ci8 N(0, 16^2) clipped to +-127, "
                     f"16-tap PPF -> 64 ch, N={w.N}; int8 MFMA X stage with int32 sums",
@@ -774,10 +779,10 @@ def main():
         x_peak, x_unit = INT8_MFMA_PEAK_TOPS, "TOP/s"
     else:
         x_mfma_tflops = cmacs * 8 / (x_ms_avg * 1e-3) / 1e12
-        x_peak, x_unit = FP32_VALU_PEAK_TFLOPS, "TFLOP/s"
+        x_peak, x_unit = FP32_MFMA_PEAK_TFLOPS, "TFLOP/s"
     x_bytes = w.SB * w.C * w.M * w.n_c * chan_b
     f_kernel = f"fstage_kernel<{w.sample_type}, {w.x_mode}, {w.C}>"
-    x_kernel = f"xstage_mfma_kernel<{w.x_mode}, {(w.M + 31) // 32}>" if w.x_mode != synth.X_FP32 else "xstage_fp32_kernel"
+    x_kernel = x_kernel_name(w)
     if w.x_mode == synth.X_INT8:
         # 4 B per sample against ~100 flop: the 8-bit F stage is bound by vector arithmetic
         f_tf = samples * F_FLOP_PER_SAMPLE / (f_ms_avg * 1e-3) / 1e12
@@ -792,7 +797,7 @@ def main():
                   "of_plain_copy": None if copy_gbs is None else round(f_gbs / copy_gbs, 4)}
         if fanout_gbs is not None and chan_b == 2 * sample_b:
             f_roof["of_same_mix_copy"] = round(f_gbs / fanout_gbs, 4)    # 1 read : 2 written
-    x_roof = {"bound": "mfma" if w.x_mode != synth.X_FP32 else "alu", "achieved": round(x_mfma_tflops, 1),
+    x_roof = {"bound": "mfma", "achieved": round(x_mfma_tflops, 1),
               "peak": x_peak, "unit": x_unit, "frac": round(x_mfma_tflops / x_peak, 4),
               "traffic": measured_traffic(x_kernel), "kernel": x_kernel, "ms": round(x_ms_avg, 4),
               "operand_gbs": round(x_bytes / (x_ms_avg * 1e-3) / 1e9, 1),
@@ -840,8 +845,8 @@ def main():
                 "real_time_factor": round(bw.N / synth.SAMPLE_RATE_HZ / ((float(np.mean(bf_ms)) + b_ms) * 1e-3), 2),
                 "roofline": {"bound": "mfma", "achieved": round(mfma_tf, 1), "peak": FP16_MFMA_PEAK_TFLOPS,
                              "unit": "TFLOP/s", "frac": round(mfma_tf / FP16_MFMA_PEAK_TFLOPS, 4),
-                             "traffic": measured_traffic(f"beam_kernel<{(bw.S + 7) // 8}, 1, false>"),
-                             "kernel": f"beam_kernel<{(bw.S + 7) // 8}, 1, false>", "algorithmic_bytes": xf["beam_bytes"]}}
+                             "traffic": measured_traffic(f"beam_kernel<{(bw.S + 7) // 8}, 1, false, 4>"),
+                             "kernel": f"beam_kernel<{(bw.S + 7) // 8}, 1, false, 4>", "algorithmic_bytes": xf["beam_bytes"]}}
         if probe is not None:
             beam["roofline"]["of_mfma_probe"] = round(mfma_tf / probe["fp16_tflops"], 4)
         t_gbs = (xf["voltage_bytes"] + xf["stokes_bytes"]) / (xf["transform_ms"] * 1e-3) / 1e9
@@ -854,8 +859,8 @@ def main():
             "transform_voltages_ms": round(xf["transform_voltages_ms"], 3),
             "transform_voltages_gbs": round(tv_gbs, 1),
             "roofline": {"bound": "hbm", "achieved": round(t_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                         "frac": round(t_gbs / HBM_PEAK_GBS, 4), "kernel": "beam_transform_kernel<16, 1>",
-                         "traffic": measured_traffic("beam_transform_kernel<16, 1>"),
+                         "frac": round(t_gbs / HBM_PEAK_GBS, 4), "kernel": "beam_transform_kernel<16, 1, false>",
+                         "traffic": measured_traffic("beam_transform_kernel<16, 1, false>"),
                          "algorithmic_bytes": xf["voltage_bytes"] + xf["stokes_bytes"]}}
         log(f"bench: beam voltages {xf['voltages_ms']:.3f} ms, transform to 16 channels {xf['transform_ms']:.3f} ms "
             f"({t_gbs:.0f} GB/s), writing voltages {xf['transform_voltages_ms']:.3f} ms ({tv_gbs:.0f} GB/s)")

@@ -20,8 +20,7 @@
  *    enqueues work and returns; results are ready when the stream reaches that point.
  *  - Stateful calls (cobalt_correlate(_ex), cobalt_channelize(_ex), cobalt_beamform,
  *    cobalt_reset_history: they use the
- *    FIR history, the delay staging and, for cobalt_correlate, the plan's channelised
- *    buffer) are ordered among themselves even across streams (the plan waits on its
+ *    FIR history and, for cobalt_correlate, the plan's channelised buffer) are ordered among themselves even across streams (the plan waits on its
  *    previous stateful call's completion event); two host threads must not make stateful
  *    calls on one plan at the same time (COBALT_EBUSY).
  *  - Stateless calls (cobalt_correlate_channelized, cobalt_beamform_channelized,
@@ -127,7 +126,7 @@ typedef struct cobalt_plan_info {
 } cobalt_plan_info;
 
 /* Create a plan on the current HIP device: validates cfg, allocates the device workspace
- * (channelised buffer, two FIR-history buffers zeroed, tables, delay staging) and copies
+ * (channelised buffer, two FIR-history buffers zeroed, tables) and copies
  * the host tables.  On success *out owns everything; on failure *out is NULL and nothing
  * is leaked.  Errors: EINVAL, EUNSUPPORTED, EOVERFLOW, ENOMEM, EDEVICE. */
 int cobalt_plan_create(const cobalt_config* cfg, cobalt_plan** out);

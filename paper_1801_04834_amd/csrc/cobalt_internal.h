@@ -15,7 +15,7 @@ constexpr int kT = 16;
 constexpr int kHistRows = kT - 1;              // FIR history in rows of C samples
 constexpr int kKBlock = 32;                    // channel samples per K block of the channelised layout
 constexpr int kPitchAlign = kKBlock;           // channelised rows padded to whole K blocks
-constexpr int kMaxMfmaInputs = 160;            // 5 row blocks of 32 (80 stations)
+constexpr int kMaxMfmaInputs = 160;            // 10 row blocks of 16 (80 stations)
 constexpr int kMaxFp32Inputs = 256;
 // Per-call host arrays (delays, coarse offsets) travel in the kernel arguments: at most 128
 // stations x 20 bytes, well inside the 4 KB a launch may carry.

@@ -1,5 +1,5 @@
 // C ABI of libcobalt.so (declared in include/cobalt.h): plan validation, device workspace,
-// FIR history, per-call delay staging and kernel launches.
+// FIR history, per-call delays (carried in the kernel arguments) and kernel launches.
 //
 // The paper wraps every GPU kernel in a class that owns its launch configuration and
 // buffer sizes and documents which buffers each kernel reads and writes ("Signal

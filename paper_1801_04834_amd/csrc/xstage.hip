@@ -58,7 +58,7 @@ constexpr int tile_I(int R, int idx) {
 constexpr int kRowB = 256;                    // LDS bytes per row and chunk (16 granules of 16 B)
 
 // LDS rows are XOR-swizzled in 16-byte granules (granule g of row r is stored at g ^ (r%16)),
-// so the 32 rows of one MFMA fragment read hit distinct banks without padding.
+// so the 16 rows of one MFMA fragment read hit distinct banks without padding.
 __device__ __forceinline__ int lds_off(int row, int g) { return row * kRowB + ((g ^ (row & 15)) << 4); }
 
 // (re, im) -> (-im, re) on packed fp16 pairs
