@@ -114,10 +114,17 @@ __global__ __launch_bounds__(512) void apply_gains_adjoint_kernel(const float2* 
 
 hipError_t launch_apply_gains(const void* vis0, const void* gains, void* vis, int n_chan, int S, hipStream_t st) {
     const int B = S * (S + 1) / 2, per_ch = (2 * B + 255) / 256;
-    if (n_chan == 0) return hipSuccess;
-    hipLaunchKernelGGL(apply_gains_kernel, dim3((unsigned)((int64_t)n_chan * per_ch)), dim3(256), 0, st, (const float4*)vis0,
-                       (const float2*)gains, (float4*)vis, B, 2 * S, per_ch);
-    return hipGetLastError();
+    // whole workgroups per channel: with few stations and millions of channels in pieces, since a
+    // launch holds fewer than 2^32 work-items
+    const int piece = (1 << 22) / per_ch;
+    hipError_t e = hipSuccess;
+    for (int64_t c0 = 0; c0 < n_chan && e == hipSuccess; c0 += piece) {
+        const int64_t n = n_chan - c0 < piece ? n_chan - c0 : piece;
+        hipLaunchKernelGGL(apply_gains_kernel, dim3((unsigned)(n * per_ch)), dim3(256), 0, st, (const float4*)vis0 + c0 * 2 * B,
+                           (const float2*)gains + c0 * 2 * S, (float4*)vis + c0 * 2 * B, B, 2 * S, per_ch);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 hipError_t launch_apply_gains_adjoint(const void* vis0, const void* gains, const void* grad_vis, void* grad_gains, int n_chan,

@@ -329,8 +329,23 @@ XArgs make_xargs(const Sizes& z, const cobalt_config& cfg, const void* d_chan, v
     return a;
 }
 
+// The FP32 form runs up to two workgroups of 512 threads per channel: more than 2^21 channels go in
+// pieces, since a launch holds fewer than 2^32 work-items.
 int launch_x(const cobalt_config& cfg, const XArgs& a, hipStream_t st) {
-    hipError_t e = cfg.x_mode == COBALT_X_FP32 ? launch_xstage_fp32(a, st) : launch_xstage_mfma(cfg.x_mode, a, st);
+    hipError_t e = hipSuccess;
+    if (cfg.x_mode != COBALT_X_FP32) {
+        e = launch_xstage_mfma(cfg.x_mode, a, st);
+    } else {
+        constexpr int kPiece = 1 << 21;
+        XArgs b = a;
+        const int64_t vis_ch = (int64_t)a.S * (a.S + 1) / 2 * 4 * 8;
+        for (int64_t c0 = 0; c0 < a.n_chan && e == hipSuccess; c0 += kPiece) {
+            b.chan = (const char*)a.chan + c0 * a.chan_stride;
+            b.vis = (char*)a.vis + c0 * vis_ch;
+            b.n_chan = (int)(a.n_chan - c0 < kPiece ? a.n_chan - c0 : kPiece);
+            e = launch_xstage_fp32(b, st);
+        }
+    }
     if (e != hipSuccess) return hip_fail(e, "X-stage launch");
     return COBALT_OK;
 }
