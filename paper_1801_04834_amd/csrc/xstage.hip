@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "cobalt_internal.h"
+#include "xring.h"
 
 namespace cobalt {
 namespace {
@@ -44,7 +45,6 @@ template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_impl<0, N>(f); }
 
 // Lower-triangle tiles of an R x R block grid, column-major: (0,0),(1,0)..(R-1,0),(1,1)..
-constexpr int tile_count(int R) { return R * (R + 1) / 2; }
 constexpr int tile_J(int R, int idx) {
     int J = 0;
     while (idx >= R - J) { idx -= R - J; ++J; }
@@ -55,7 +55,6 @@ constexpr int tile_I(int R, int idx) {
     while (idx >= R - J) { idx -= R - J; ++J; }
     return J + idx;
 }
-constexpr int kRowB = 256;                    // LDS bytes per row and chunk (16 granules of 16 B)
 
 // LDS rows are XOR-swizzled in 16-byte granules (granule g of row r is stored at g ^ (r%16)),
 // so the 16 rows of one MFMA fragment read hit distinct banks without padding.
@@ -83,17 +82,6 @@ __device__ __forceinline__ uintx4 swapneg_i8(uintx4 d) {
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
 // ------------------------------------------------------------------ LDS ring ---
-// Chunks (one K block in FP32 and FP16-split mode, four in int8 mode; 256 bytes per row) stream
-// global -> LDS through a ring of `depth` stages of `nch` chunks, depth - 1 of them in flight.
-// Only ceil(M/4)*4 rows are kept per chunk; fragment reads of a row block's padding rows fall on
-// whatever follows inside the LDS array, and only reach outputs that are never stored.
-struct XRing {
-    int nch, depth;          // chunks per stage, stages
-    int n_inst, ipw;         // 1 KB transfers per chunk, transfers per wave and (full) stage
-    int chunk_b;             // bytes per chunk
-    int n_chunk;             // chunks of a channel
-};
-
 // Wait until at most n of this wave's transfers are outstanding (rounded down to the counts
 // built: a smaller count waits longer, never shorter).
 __device__ __forceinline__ void wait_transfers(int n) {
@@ -146,27 +134,6 @@ __device__ __forceinline__ void ring_issue(const XArgs& a, const XRing& q, const
     }
 }
 
-// Host: ring of at most lds_b bytes (minus `slack` bytes that fragment reads may run past the
-// last chunk).  Stages of about 8 KB per wave keep the barriers few; the depth takes the rest.
-XRing make_ring(int mode, const XArgs& a, int waves, int lds_b, int slack, int nch_multiple) {
-    XRing q{};
-    const int kc = mode == XM_INT8 ? 128 : 32;
-    q.n_chunk = (a.n_c + kc - 1) / kc;
-    q.n_inst = (a.M + 3) / 4;
-    q.chunk_b = q.n_inst * 1024;
-    const int room = (lds_b - slack) / q.chunk_b;                  // chunks that fit
-    int nch = room / 3;                                            // three stages or more
-    nch = nch / nch_multiple * nch_multiple;
-    nch = nch < 1 ? (room >= 2 * nch_multiple ? nch_multiple : 1) : nch > 8 ? 8 : nch;
-    while (nch > nch_multiple && nch * q.n_inst > 8 * waves) nch -= nch_multiple;
-    q.nch = nch;
-    q.ipw = (nch * q.n_inst + waves - 1) / waves;
-    q.depth = room / nch;
-    while (q.depth > 3 && (q.depth - 2) * q.ipw > 32) --q.depth;  // counted waits are built up to 32
-    if (q.depth > 8) q.depth = 8;
-    return q;
-}
-
 // Zero columns >= n_c of the last chunk (`cols` of them from its column `first`) for rows < M.
 template <int MODE>
 __device__ __forceinline__ void zero_columns(const XArgs& a, char* buf, int first, int cols, int tid, int nthr) {
@@ -189,11 +156,10 @@ template <int MODE, int NWV, class F>
 __device__ __forceinline__ void ring_loop(const XArgs& a, const XRing& q, const char* __restrict__ chan, char* lds, int tid, F&& body) {
     constexpr int kc = MODE == XM_INT8 ? 128 : 32;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int n_stage = (q.n_chunk + q.nch - 1) / q.nch, n_full = q.n_chunk / q.nch;
-    for (int s = 0; s < min(q.depth - 1, n_stage); ++s) ring_issue<MODE, NWV>(a, q, chan, lds, s, wave, lane);
+    const int n_stage = ring_stages(q);
+    for (int s = 0; s < ring_ahead(q); ++s) ring_issue<MODE, NWV>(a, q, chan, lds, s, wave, lane);
     for (int s = 0; s < n_stage; ++s) {
-        // stages s + 1 .. s + depth - 2 may still be in flight (counted where all of them are full)
-        wait_transfers(s + q.depth - 2 < n_full ? q.ipw * (q.depth - 2) : 0);
+        wait_transfers(ring_may_fly(q, s));
         lds_barrier();                        // ... for every wave; the slot of stage s - 1 is free
         if (s + q.depth - 1 < n_stage) ring_issue<MODE, NWV>(a, q, chan, lds, s + q.depth - 1, wave, lane);
         char* buf = lds + (s % q.depth) * (q.nch * q.chunk_b);
@@ -223,20 +189,13 @@ __device__ __forceinline__ void ring_loop(const XArgs& a, const XRing& q, const 
 // 5 row blocks of 32), us, FP16-split: 24 st x 32 SB 604 -> 428 (5.7 TB/s); 48 x 16 640 -> 545;
 // 52 x 61 2905 -> 2240; 76 x 64 4030 -> 3780; 24 x 1 125 -> 49; 48 x 1 at 256 channels 54 -> 36.
 // int8: 24 x 32 143 -> 112; 76 x 64 944 -> 932.
-template <int MODE, int NB, int NWV> constexpr int ks_groups() {
-    if (NB <= 3) return 1;
-    if (NB <= 5) return NWV == 8 ? 2 : 1;
-    if (NB <= 7) return 2;
-    return NB == 8 && MODE == XM_INT8 ? 2 : 4;
-}
 template <int MODE, int NB, int NWV> constexpr int ks_per() {
-    return (tile_count(NB) + ks_groups<MODE, NB, NWV>() - 1) / ks_groups<MODE, NB, NWV>();
+    return (tile_count(NB) + ks_groups(MODE == XM_INT8, NB, NWV) - 1) / ks_groups(MODE == XM_INT8, NB, NWV);
 }
 template <int MODE, int NB, int NWV, int G> constexpr int ks_tiles() {
     const int left = tile_count(NB) - G * ks_per<MODE, NB, NWV>();
     return left < ks_per<MODE, NB, NWV>() ? left : ks_per<MODE, NB, NWV>();
 }
-template <int NB, int NWV> constexpr int ks_lds() { return NWV == 8 ? 163840 : NB <= 2 ? 40960 : NB == 3 ? 53248 : 81920; }
 template <int NB, int NWV> constexpr int ks_waves_per_simd() { return NWV == 8 ? 2 : NB <= 2 ? 4 : NB == 3 ? 3 : 2; }
 // row blocks used by tiles [t0, t0 + n)
 constexpr unsigned ks_blocks(int NB, int t0, int n) {
@@ -247,11 +206,11 @@ constexpr unsigned ks_blocks(int NB, int t0, int n) {
 
 template <int MODE> struct KCfg;
 template <> struct KCfg<XM_FP16_SPLIT> {
-    static constexpr int kSteps = 2;          // k-steps of 16 samples per chunk
+    static constexpr int kSteps = ks_steps(false);
     using acc_t = floatx4;
 };
 template <> struct KCfg<XM_INT8> {
-    static constexpr int kSteps = 4;          // k-steps of 32 samples per chunk
+    static constexpr int kSteps = ks_steps(true);
     using acc_t = intx4;
 };
 
@@ -298,7 +257,7 @@ template <int MODE, int NB, int NWV, int G>
 __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const char* __restrict__ chan, char* lds, int tid) {
     using acc_t = typename KCfg<MODE>::acc_t;
     constexpr int kSteps = KCfg<MODE>::kSteps;
-    constexpr int kTG = ks_groups<MODE, NB, NWV>(), kPer = ks_per<MODE, NB, NWV>(), T0 = G * kPer, NT = ks_tiles<MODE, NB, NWV, G>(), kKP = NWV / kTG;
+    constexpr int kTG = ks_groups(MODE == XM_INT8, NB, NWV), kPer = ks_per<MODE, NB, NWV>(), T0 = G * kPer, NT = ks_tiles<MODE, NB, NWV, G>(), kKP = ks_parts(MODE == XM_INT8, NB, NWV);
     constexpr unsigned kUsed = ks_blocks(NB, T0, NT);
     constexpr bool kDiagHl = MODE == XM_FP16_SPLIT && kKP == 1;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, kpart = wave / kTG;
@@ -310,11 +269,17 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
     acc_t xre[kDiagHl ? kPer : 1], xim[kDiagHl ? kPer : 1];             // h l^T of diagonal tiles
 #pragma unroll
     for (int t = 0; t < (kDiagHl ? kPer : 1); ++t) xre[t] = xim[t] = acc_t{};
-    // the last row block's padding rows read zeros kept behind the ring (a zero operand also spares
-    // the matrix pipes' power)
-    const bool pad = 16 * (NB - 1) + row >= a.M;
-    const char* zeros = lds + ks_lds<NB, NWV>() - 256;
-    if (tid < 16) *(uint4*)(lds + ks_lds<NB, NWV>() - 256 + tid * 16) = make_uint4(0, 0, 0, 0);
+    // the last row block's padding rows: the row of zeros behind the ring, or, where the chunks hold
+    // them, rows of every slot that no transfer writes
+    const int kept = 4 * q.n_inst - a.M;                                // padding rows in a chunk
+    const bool behind = 4 * q.n_inst < 16 * NB, pad = behind && 16 * (NB - 1) + row >= a.M;
+    const char* zeros = lds + ks_lds(NB, NWV) - kRowB;
+    if (behind) {
+        if (tid < 16) *(uint4*)(lds + ks_lds(NB, NWV) - kRowB + tid * 16) = make_uint4(0, 0, 0, 0);
+    } else {
+        for (int i = tid; i < q.depth * q.nch * kept * 16; i += 64 * NWV)
+            *(uint4*)(lds + i / (kept * 16) * q.chunk_b + a.M * kRowB + i % (kept * 16) * 16) = make_uint4(0, 0, 0, 0);
+    }
 
     ring_loop<MODE, NWV>(a, q, chan, lds, tid, [&](char* buf, int nch) {
         for (int id = kpart; id < nch * kSteps; id += kKP) {
@@ -368,7 +333,7 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
 
     // ---- sums over the k parts; every wave ends with a share of its group's tiles ----
     constexpr int kStride = kTG * ((kPer + 1) / 2) * 2 * 64;            // accumulators between k parts' areas
-    static_assert(kKP == 1 || kKP * kStride * 16 <= ks_lds<NB, NWV>(), "partial sums inside LDS");
+    static_assert(kKP == 1 || kKP * kStride * 16 <= ks_lds(NB, NWV), "partial sums inside LDS");
     int t_own = T0, n_own = NT;
     ks_reduce<kPer, kKP>(re, im, (acc_t*)lds + kpart * kStride + G * (kStride / kTG), kpart, kStride, lane, t_own, n_own);
 
@@ -430,45 +395,43 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
 
 template <int MODE, int NB, int NWV>
 __global__ __launch_bounds__(64 * NWV, (ks_waves_per_simd<NB, NWV>())) void xstage_ksplit_kernel(XArgs a, XRing q) {
-    __shared__ __attribute__((aligned(1024))) char lds[ks_lds<NB, NWV>()];
+    __shared__ __attribute__((aligned(1024))) char lds[ks_lds(NB, NWV)];
     const int tid = threadIdx.x;
     const char* chan = (const char*)a.chan + (int64_t)blockIdx.x * a.chan_stride;
-    const int g = __builtin_amdgcn_readfirstlane(tid >> 6) % ks_groups<MODE, NB, NWV>();
-    static_for<ks_groups<MODE, NB, NWV>()>([&](auto gi) {
+    const int g = __builtin_amdgcn_readfirstlane(tid >> 6) % ks_groups(MODE == XM_INT8, NB, NWV);
+    static_for<ks_groups(MODE == XM_INT8, NB, NWV)>([&](auto gi) {
         constexpr int G = decltype(gi)::value;
         if (g == G) xks_wave<MODE, NB, NWV, G>(a, q, chan, lds, tid);
     });
 }
 
 template <int MODE, int NB, int NWV>
-void launch_ksplit(const XArgs& a, hipStream_t st) {
-    // a stage holds a multiple of the k-steps that the waves of a group share
-    constexpr int parts = NWV / ks_groups<MODE, NB, NWV>(), mult = parts > KCfg<MODE>::kSteps ? parts / KCfg<MODE>::kSteps : 1;
-    const XRing q = make_ring(MODE, a, NWV, ks_lds<NB, NWV>() - 256, (16 * NB - (a.M + 3) / 4 * 4) * kRowB, mult);
+hipError_t launch_ksplit(const XArgs& a, hipStream_t st) {
+    const XRing q = ks_ring(MODE == XM_INT8, NB, NWV, a.M, a.n_c);
+    if (!ring_ok(q, KCfg<MODE>::kSteps, ks_parts(MODE == XM_INT8, NB, NWV))) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((xstage_ksplit_kernel<MODE, NB, NWV>), dim3((unsigned)a.n_chan), dim3(64 * NWV), 0, st, a, q);
+    return hipGetLastError();
 }
 template <int MODE, int NB>
-void launch_ksplit(const XArgs& a, hipStream_t st) {
-    if (a.n_chan <= kCUs) launch_ksplit<MODE, NB, 8>(a, st);
-    else launch_ksplit<MODE, NB, 4>(a, st);
+hipError_t launch_ksplit(const XArgs& a, hipStream_t st) {
+    return a.n_chan <= kCUs ? launch_ksplit<MODE, NB, 8>(a, st) : launch_ksplit<MODE, NB, 4>(a, st);
 }
 
 template <int MODE>
 hipError_t launch_mode(const XArgs& a, hipStream_t st) {
     switch ((a.M + 15) / 16) {
-        case 1: launch_ksplit<MODE, 1>(a, st); break;
-        case 2: launch_ksplit<MODE, 2>(a, st); break;
-        case 3: launch_ksplit<MODE, 3>(a, st); break;
-        case 4: launch_ksplit<MODE, 4>(a, st); break;
-        case 5: launch_ksplit<MODE, 5>(a, st); break;
-        case 6: launch_ksplit<MODE, 6>(a, st); break;
-        case 7: launch_ksplit<MODE, 7>(a, st); break;
-        case 8: launch_ksplit<MODE, 8>(a, st); break;
-        case 9: launch_ksplit<MODE, 9>(a, st); break;
-        case 10: launch_ksplit<MODE, 10>(a, st); break;
+        case 1: return launch_ksplit<MODE, 1>(a, st);
+        case 2: return launch_ksplit<MODE, 2>(a, st);
+        case 3: return launch_ksplit<MODE, 3>(a, st);
+        case 4: return launch_ksplit<MODE, 4>(a, st);
+        case 5: return launch_ksplit<MODE, 5>(a, st);
+        case 6: return launch_ksplit<MODE, 6>(a, st);
+        case 7: return launch_ksplit<MODE, 7>(a, st);
+        case 8: return launch_ksplit<MODE, 8>(a, st);
+        case 9: return launch_ksplit<MODE, 9>(a, st);
+        case 10: return launch_ksplit<MODE, 10>(a, st);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ plain FP32 form ---
@@ -491,14 +454,7 @@ hipError_t launch_mode(const XArgs& a, hipStream_t st) {
 // growing sum); partial sums of b samples folded into the totals leave about
 // u (b / sqrt(N_c) + sqrt(N_c / b)) / 6, smallest near b = sqrt(N_c): 7.7 times less at
 // N_c = 3072 and b = 128.
-constexpr int kF32Waves = 8;
-constexpr int kF32LdsB = 147456;
 constexpr int kF32Fold = 16;                  // k-steps of 8 samples
-constexpr int kF32MaxTpw = 9;                 // 144 accumulator registers, two waves per SIMD
-
-struct XF32 {
-    int n_tiles, nb, groups, n_tg;
-};
 
 template <int TPW>
 __global__ __launch_bounds__(64 * kF32Waves, 2) void xstage_f32_kernel(XArgs a, XRing q, XF32 f) {
@@ -634,28 +590,12 @@ hipError_t launch_xstage_mfma(int x_mode, const XArgs& a, hipStream_t st) {
 
 hipError_t launch_xstage_fp32(const XArgs& a, hipStream_t st) {
     if (a.n_chan <= 0) return hipSuccess;
-    XF32 f{};
-    f.nb = (a.M + 15) / 16;
-    f.n_tiles = f.nb * (f.nb + 1) / 2;
-    // Split with the least time per CU: rounds of workgroups x tile slots per channel share.  Every
-    // workgroup of a channel reads all of it, so there are several only where their tiles need them
-    // (more than 8 x 9 tiles) or CUs would idle otherwise (40 stations, 512 channels: three workgroups
-    // waste no slot and take 690 us, one takes 480); ties go to fewer groups of waves, whose waves
-    // hold more tiles per barrier (40 stations: 478 us with two groups, 517 with eight).
-    int best = 0x7fffffff, tpw = 1;
-    const int least = (f.n_tiles + kF32Waves * kF32MaxTpw - 1) / (kF32Waves * kF32MaxTpw);
-    for (int groups = least; groups <= 4 && (groups == least || (int64_t)a.n_chan * groups <= kCUs); ++groups)
-        for (int n_tg = 1; n_tg <= kF32Waves; n_tg *= 2) {
-            const int per = (f.n_tiles + groups * n_tg - 1) / (groups * n_tg);
-            if (per > kF32MaxTpw) continue;
-            const int64_t rounds = ((int64_t)a.n_chan * groups + kCUs - 1) / kCUs;
-            const int64_t cost = rounds * per * n_tg;
-            if (cost < best) { best = (int)cost; tpw = per; f.groups = groups; f.n_tg = n_tg; }
-        }
-    const int n_kp = kF32Waves / f.n_tg;
-    const XRing q = make_ring(XM_FP32, a, kF32Waves, kF32LdsB, (16 * f.nb - (a.M + 3) / 4 * 4) * kRowB, n_kp == 8 ? 2 : 1);
+    const XF32 f = f32_split(a.M, a.n_chan, kCUs);
+    if (f.n_tg < 1) return hipErrorInvalidConfiguration;
+    const XRing q = f32_ring(f, a.M, a.n_c);
+    if (!ring_ok(q, kF32Steps, kF32Waves / f.n_tg)) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)((int64_t)a.n_chan * f.groups)), block(64 * kF32Waves);
-    switch (tpw) {
+    switch (f.tpw) {
         case 1: hipLaunchKernelGGL(xstage_f32_kernel<1>, grid, block, 0, st, a, q, f); break;
         case 2: hipLaunchKernelGGL(xstage_f32_kernel<2>, grid, block, 0, st, a, q, f); break;
         case 3: hipLaunchKernelGGL(xstage_f32_kernel<3>, grid, block, 0, st, a, q, f); break;
