@@ -13,11 +13,12 @@
 // A' is built in registers from the B-role fragments.
 //   FP16-split: Z*2^k = hi + lo (two fp16 planes); V ~= hh + hl + lh accumulated in FP32
 //   (the dropped lo*lo term is below 2^-22 of |Z|^2), scaled back by 2^-2k.  A diagonal tile (I = J)
-//   needs h h^T + h l^T + l h^T: it accumulates W = h (h + 2 l)^T in two products (2 l is exact) and
-//   takes (W + W^T) / 2 (real part) or (W - W^T) / 2 (imaginary part) at the end.  Where a wave sums
-//   all k-steps itself, h l^T has accumulators of its own: the MFMAs round towards zero, and the long
-//   sums of the autos would otherwise be rounded twice per k-step (relative error against 64 bits at
-//   76 stations 7.3e-7 instead of 4.7e-7).
+//   needs h h^T + h l^T + l h^T: it accumulates h h^T and X = h l^T in two products and adds
+//   X + X^T (real part) or X - X^T (imaginary part) at the end.  X has accumulators of its own: one
+//   sum of h (h + 2 l)^T would need none, but 2 l overflows FP16 for lo values above 32752, which a
+//   channelised buffer filled by the caller may hold, and the MFMAs round towards zero, twice per
+//   k-step of the long sums of the autos (relative error against 64 bits at 76 stations 7.3e-7
+//   instead of 4.7e-7).
 //   int8: exact int32 sums.
 // Plain FP32 form: the same two contractions on FP32 operands and FP32 MFMAs over 16x16 tiles, with
 // partial sums over 128 channel samples folded into running totals.
@@ -259,16 +260,16 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
     constexpr int kSteps = KCfg<MODE>::kSteps;
     constexpr int kTG = ks_groups(MODE == XM_INT8, NB, NWV), kPer = ks_per<MODE, NB, NWV>(), T0 = G * kPer, NT = ks_tiles<MODE, NB, NWV, G>(), kKP = ks_parts(MODE == XM_INT8, NB, NWV);
     constexpr unsigned kUsed = ks_blocks(NB, T0, NT);
-    constexpr bool kDiagHl = MODE == XM_FP16_SPLIT && kKP == 1;
+    constexpr bool kSplit = MODE == XM_FP16_SPLIT;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, kpart = wave / kTG;
     const int row = lane & 15, kg = lane >> 4;
 
     acc_t re[kPer], im[kPer];
 #pragma unroll
     for (int t = 0; t < kPer; ++t) re[t] = im[t] = acc_t{};
-    acc_t xre[kDiagHl ? kPer : 1], xim[kDiagHl ? kPer : 1];             // h l^T of diagonal tiles
+    acc_t xre[kSplit ? kPer : 1], xim[kSplit ? kPer : 1];               // h l^T of diagonal tiles
 #pragma unroll
-    for (int t = 0; t < (kDiagHl ? kPer : 1); ++t) xre[t] = xim[t] = acc_t{};
+    for (int t = 0; t < (kSplit ? kPer : 1); ++t) xre[t] = xim[t] = acc_t{};
     // the last row block's padding rows: the row of zeros behind the ring, or, where the chunks hold
     // them, rows of every slot that no transfer writes
     const int kept = 4 * q.n_inst - a.M;                                // padding rows in a chunk
@@ -296,22 +297,27 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
                         fl[b] = *(const uintx4*)(b == NB - 1 ? last + to_lo : base_lo + 16 * b * kRowB);
                     }
                 });
-                static_for<3>([&](auto pi) {
-                    constexpr int pr = decltype(pi)::value;
-                    static_for<NT>([&](auto t_) {
-                        constexpr int t = decltype(t_)::value;
-                        constexpr int I = tile_I(NB, T0 + t), J = tile_J(NB, T0 + t);
-                        if constexpr (!(I == J && pr == 2)) {
-                            const half8 A = __builtin_bit_cast(half8, pr == 2 ? fl[I] : fh[I]);
-                            half8 B = __builtin_bit_cast(half8, pr == 1 ? fl[J] : fh[J]);
-                            if constexpr (I == J && pr == 1 && !kDiagHl) B = B + B;
-                            const half8 Bs = __builtin_bit_cast(half8, swapneg_f16(__builtin_bit_cast(uintx4, B)));
-                            acc_t& R = I == J && pr == 1 && kDiagHl ? xre[kDiagHl ? t : 0] : re[t];
-                            acc_t& Q = I == J && pr == 1 && kDiagHl ? xim[kDiagHl ? t : 0] : im[t];
-                            R = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, B, R, 0, 0, 0);
-                            Q = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, Bs, Q, 0, 0, 0);
-                        }
+                // column by column, kept apart: the swapped operands of one column are live at a time
+                // (all at once spill at 5 row blocks; 40 stations x 16 subbands 685 us against 379)
+                static_for<NB>([&](auto ji) {
+                    constexpr int J = decltype(ji)::value;
+                    static_for<3>([&](auto pi) {
+                        constexpr int pr = decltype(pi)::value;
+                        static_for<NT>([&](auto t_) {
+                            constexpr int t = decltype(t_)::value;
+                            constexpr int I = tile_I(NB, T0 + t);
+                            if constexpr (tile_J(NB, T0 + t) == J && !(I == J && pr == 2)) {
+                                const half8 A = __builtin_bit_cast(half8, pr == 2 ? fl[I] : fh[I]);
+                                const half8 B = __builtin_bit_cast(half8, pr == 1 ? fl[J] : fh[J]);
+                                const half8 Bs = __builtin_bit_cast(half8, swapneg_f16(__builtin_bit_cast(uintx4, B)));
+                                acc_t& R = I == J && pr == 1 ? xre[t] : re[t];
+                                acc_t& Q = I == J && pr == 1 ? xim[t] : im[t];
+                                R = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, B, R, 0, 0, 0);
+                                Q = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, Bs, Q, 0, 0, 0);
+                            }
+                        });
                     });
+                    __builtin_amdgcn_sched_barrier(0);
                 });
             } else {
                 uintx4 f[NB];
@@ -330,6 +336,17 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
             }
         }
     });
+
+    // several k parts: W = h h^T + 2 X takes one place in the sums, and W + W^T = 2 (h h^T + X + X^T)
+    if constexpr (kSplit && kKP > 1) {
+        static_for<NT>([&](auto t_) {
+            constexpr int t = decltype(t_)::value;
+            if constexpr (tile_I(NB, T0 + t) == tile_J(NB, T0 + t)) {
+                re[t] += 2.f * xre[t];
+                im[t] += 2.f * xim[t];
+            }
+        });
+    }
 
     // ---- sums over the k parts; every wave ends with a share of its group's tiles ----
     constexpr int kStride = kTG * ((kPer + 1) / 2) * 2 * 64;            // accumulators between k parts' areas
@@ -352,10 +369,9 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
         acc_t vr = re[t], vi = im[t];
         if constexpr (MODE == XM_FP16_SPLIT) {
             if (I == J) {
-                // (W + W^T) / 2 and (W - W^T) / 2, or h h^T + X + X^T and h h^T + X - X^T with
-                // X = h l^T; the same wave reads its transpose back (its LDS operations complete in
-                // order)
-                const acc_t wr = kDiagHl ? xre[kDiagHl ? t : 0] : vr, wi = kDiagHl ? xim[kDiagHl ? t : 0] : vi;
+                // h h^T + X + X^T and h h^T + X - X^T, or (W + W^T) / 2 and (W - W^T) / 2; the same
+                // wave reads its transpose back (its LDS operations complete in order)
+                const acc_t wr = kKP == 1 ? xre[t] : vr, wi = kKP == 1 ? xim[t] : vi;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     tr[(4 * kg + r) * 17 + row] = wr[r];
@@ -364,8 +380,8 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float sr = wr[r] + tr[row * 17 + 4 * kg + r], si = wi[r] - tr[16 * 17 + row * 17 + 4 * kg + r];
-                    vr[r] = kDiagHl ? vr[r] + sr : 0.5f * sr;
-                    vi[r] = kDiagHl ? vi[r] + si : 0.5f * si;
+                    vr[r] = kKP == 1 ? vr[r] + sr : 0.5f * sr;
+                    vi[r] = kKP == 1 ? vi[r] + si : 0.5f * si;
                 }
             }
             vr *= a.out_scale;
