@@ -102,14 +102,13 @@ __device__ __forceinline__ void wait_transfers(int n) {
 // this wave's LDS reads and writes are complete before it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Issue stage s into its ring slot.  Every wave issues exactly ipw transfers of a full stage (the
+// Issue stage s into its ring slot at buf.  Every wave issues exactly ipw transfers of a full stage (the
 // last ones repeat the stage's final transfer), so that counted waits hold for every wave; the
 // last, partial stage may issue fewer.
 template <int MODE, int NWV>
-__device__ __forceinline__ void ring_issue(const XArgs& a, const XRing& q, const char* __restrict__ chan, char* lds, int s, int wave,
+__device__ __forceinline__ void ring_issue(const XArgs& a, const XRing& q, const char* __restrict__ chan, char* buf, int s, int wave,
                                            int lane) {
     const int c0 = s * q.nch, nch = min(q.nch, q.n_chunk - c0);
-    char* buf = lds + (s % q.depth) * (q.nch * q.chunk_b);
     const int rsub = lane >> 4, p = lane & 15;
     int ck = 0, i = wave;
     for (int k = 0; k < q.ipw; ++k, i += NWV) {
@@ -151,21 +150,24 @@ __device__ __forceinline__ void zero_columns(const XArgs& a, char* buf, int firs
     }
 }
 
-// The ring's loop over a channel: body(stage buffer, chunks in the stage, stage index) runs with
+// The ring's loop over a channel: body(stage buffer, chunks in the stage) runs with
 // every chunk of the stage in LDS.
 template <int MODE, int NWV, class F>
 __device__ __forceinline__ void ring_loop(const XArgs& a, const XRing& q, const char* __restrict__ chan, char* lds, int tid, F&& body) {
     constexpr int kc = MODE == XM_INT8 ? 128 : 32;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int n_stage = ring_stages(q);
-    for (int s = 0; s < ring_ahead(q); ++s) ring_issue<MODE, NWV>(a, q, chan, lds, s, wave, lane);
-    for (int s = 0; s < n_stage; ++s) {
+    const int slot_b = q.nch * q.chunk_b;
+    for (int s = 0; s < ring_ahead(q); ++s) ring_issue<MODE, NWV>(a, q, chan, lds + s * slot_b, s, wave, lane);
+    int slot = 0, freed = q.depth - 1;        // slots of stage s and of stage s - 1 (and s + depth - 1)
+    for (int s = 0; s < q.n_stage; ++s) {
         wait_transfers(ring_may_fly(q, s));
         lds_barrier();                        // ... for every wave; the slot of stage s - 1 is free
-        if (s + q.depth - 1 < n_stage) ring_issue<MODE, NWV>(a, q, chan, lds, s + q.depth - 1, wave, lane);
-        char* buf = lds + (s % q.depth) * (q.nch * q.chunk_b);
+        if (s + q.depth - 1 < q.n_stage) ring_issue<MODE, NWV>(a, q, chan, lds + freed * slot_b, s + q.depth - 1, wave, lane);
+        char* buf = lds + slot * slot_b;
+        freed = slot;
+        if (++slot == q.depth) slot = 0;
         const int nch = min(q.nch, q.n_chunk - s * q.nch);
-        if (s == n_stage - 1 && a.n_c % kc != 0) {
+        if (s == q.n_stage - 1 && a.n_c % kc != 0) {
             const int first = a.n_c % kc;
             zero_columns<MODE>(a, buf + (nch - 1) * q.chunk_b, first, kc - first, tid, 64 * NWV);
             lds_barrier();
@@ -183,7 +185,7 @@ __device__ __forceinline__ void ring_loop(const XArgs& a, const XRing& q, const 
 // and the matrix pipes draw on it (24 stations x 2048 channels holds 1.70 GHz), so work that is not
 // needed costs time also where no pipe is full.  Hence tiles of 16 (48 inputs: 30 MFMAs of 16x16x32
 // per 16 samples against 28 of twice the length with tiles of 32), zeros for the padding rows and
-// two instead of three products on the diagonal.  Four waves per workgroup and two to four
+// two instead of three products on the diagonal.  Four waves per workgroup and two or more
 // workgroups per CU; with at most one channel per CU eight waves and the whole LDS as ring.
 // Groups are as few as the accumulators and fragments allow without spilling.
 // Measured against one workgroup of four waves with up to four 32 x 32 tiles each (waves idle below
@@ -261,6 +263,7 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
     constexpr int kTG = ks_groups(MODE == XM_INT8, NB, NWV), kPer = ks_per<MODE, NB, NWV>(), T0 = G * kPer, NT = ks_tiles<MODE, NB, NWV, G>(), kKP = ks_parts(MODE == XM_INT8, NB, NWV);
     constexpr unsigned kUsed = ks_blocks(NB, T0, NT);
     constexpr bool kSplit = MODE == XM_FP16_SPLIT;
+    constexpr bool kOne = NB <= 2;                                      // the waves of part 0 may do all k-steps
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, kpart = wave / kTG;
     const int row = lane & 15, kg = lane >> 4;
 
@@ -274,16 +277,16 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
     // them, rows of every slot that no transfer writes
     const int kept = 4 * q.n_inst - a.M;                                // padding rows in a chunk
     const bool behind = 4 * q.n_inst < 16 * NB, pad = behind && 16 * (NB - 1) + row >= a.M;
-    const char* zeros = lds + ks_lds(NB, NWV) - kRowB;
+    const char* zeros = lds + q.lds_b - kRowB;
     if (behind) {
-        if (tid < 16) *(uint4*)(lds + ks_lds(NB, NWV) - kRowB + tid * 16) = make_uint4(0, 0, 0, 0);
+        if (tid < 16) *(uint4*)(lds + q.lds_b - kRowB + tid * 16) = make_uint4(0, 0, 0, 0);
     } else {
-        for (int i = tid; i < q.depth * q.nch * kept * 16; i += 64 * NWV)
+        for (int i = tid; i < ring_slots(q) * kept * 16; i += 64 * NWV)
             *(uint4*)(lds + i / (kept * 16) * q.chunk_b + a.M * kRowB + i % (kept * 16) * 16) = make_uint4(0, 0, 0, 0);
     }
 
     ring_loop<MODE, NWV>(a, q, chan, lds, tid, [&](char* buf, int nch) {
-        for (int id = kpart; id < nch * kSteps; id += kKP) {
+        for (int id = kOne && kpart >= q.parts ? nch * kSteps : kpart; id < nch * kSteps; id += kOne ? q.parts : kKP) {
             const char* base = buf + (id / kSteps) * q.chunk_b + row * kRowB + (((4 * (id % kSteps) + kg) ^ row) << 4);
             const char* last = pad ? zeros : base + 16 * (NB - 1) * kRowB;
             if constexpr (MODE == XM_FP16_SPLIT) {
@@ -350,16 +353,17 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
 
     // ---- sums over the k parts; every wave ends with a share of its group's tiles ----
     constexpr int kStride = kTG * ((kPer + 1) / 2) * 2 * 64;            // accumulators between k parts' areas
-    static_assert(kKP == 1 || kKP * kStride * 16 <= ks_lds(NB, NWV), "partial sums inside LDS");
+    static_assert(kKP == 1 || kKP * kStride * 16 <= ks_sums(MODE == XM_INT8, NB, NWV), "partial sums inside LDS");
     int t_own = T0, n_own = NT;
-    ks_reduce<kPer, kKP>(re, im, (acc_t*)lds + kpart * kStride + G * (kStride / kTG), kpart, kStride, lane, t_own, n_own);
+    if (kOne && q.parts == 1) n_own = kpart == 0 ? NT : 0;
+    else ks_reduce<kPer, kKP>(re, im, (acc_t*)lds + kpart * kStride + G * (kStride / kTG), kpart, kStride, lane, t_own, n_own);
 
     // ---- stored baselines s1 >= s2, all four polarisation products ----
     const int64_t ch = blockIdx.x;
     const int64_t n_bl = (int64_t)a.S * (a.S + 1) / 2;
     float* tr = (float*)lds + wave * (2 * 16 * 17);
 #pragma unroll
-    for (int t = 0; t < ks_left(kPer, kKP); ++t) {
+    for (int t = 0; t < (kOne ? kPer : ks_left(kPer, kKP)); ++t) {
         if (t >= n_own) continue;
         int J = 0, I = t_own + t;                                       // tile t_own + t of the column-major list
         while (I >= NB - J) { I -= NB - J; ++J; }
@@ -411,7 +415,7 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
 
 template <int MODE, int NB, int NWV>
 __global__ __launch_bounds__(64 * NWV, (ks_waves_per_simd<NB, NWV>())) void xstage_ksplit_kernel(XArgs a, XRing q) {
-    __shared__ __attribute__((aligned(1024))) char lds[ks_lds(NB, NWV)];
+    extern __shared__ __attribute__((aligned(1024))) char lds[];        // q.lds_b bytes
     const int tid = threadIdx.x;
     const char* chan = (const char*)a.chan + (int64_t)blockIdx.x * a.chan_stride;
     const int g = __builtin_amdgcn_readfirstlane(tid >> 6) % ks_groups(MODE == XM_INT8, NB, NWV);
@@ -424,8 +428,8 @@ __global__ __launch_bounds__(64 * NWV, (ks_waves_per_simd<NB, NWV>())) void xsta
 template <int MODE, int NB, int NWV>
 hipError_t launch_ksplit(const XArgs& a, hipStream_t st) {
     const XRing q = ks_ring(MODE == XM_INT8, NB, NWV, a.M, a.n_c);
-    if (!ring_ok(q, KCfg<MODE>::kSteps, ks_parts(MODE == XM_INT8, NB, NWV))) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((xstage_ksplit_kernel<MODE, NB, NWV>), dim3((unsigned)a.n_chan), dim3(64 * NWV), 0, st, a, q);
+    if (!ring_ok(q, KCfg<MODE>::kSteps)) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL((xstage_ksplit_kernel<MODE, NB, NWV>), dim3((unsigned)a.n_chan), dim3(64 * NWV), q.lds_b, st, a, q);
     return hipGetLastError();
 }
 template <int MODE, int NB>
@@ -474,7 +478,7 @@ constexpr int kF32Fold = 16;                  // k-steps of 8 samples
 
 template <int TPW>
 __global__ __launch_bounds__(64 * kF32Waves, 2) void xstage_f32_kernel(XArgs a, XRing q, XF32 f) {
-    __shared__ __attribute__((aligned(1024))) char lds[kF32LdsB];
+    extern __shared__ __attribute__((aligned(1024))) char lds[];        // q.lds_b bytes
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t ch = blockIdx.x / f.groups;
@@ -606,21 +610,21 @@ hipError_t launch_xstage_mfma(int x_mode, const XArgs& a, hipStream_t st) {
 
 hipError_t launch_xstage_fp32(const XArgs& a, hipStream_t st) {
     if (a.n_chan <= 0) return hipSuccess;
-    const XF32 f = f32_split(a.M, a.n_chan, kCUs);
+    const XF32 f = f32_split(a.M, a.n_c, a.n_chan, kCUs);
     if (f.n_tg < 1) return hipErrorInvalidConfiguration;
     const XRing q = f32_ring(f, a.M, a.n_c);
-    if (!ring_ok(q, kF32Steps, kF32Waves / f.n_tg)) return hipErrorInvalidConfiguration;
+    if (!ring_ok(q, kF32Steps)) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)((int64_t)a.n_chan * f.groups)), block(64 * kF32Waves);
     switch (f.tpw) {
-        case 1: hipLaunchKernelGGL(xstage_f32_kernel<1>, grid, block, 0, st, a, q, f); break;
-        case 2: hipLaunchKernelGGL(xstage_f32_kernel<2>, grid, block, 0, st, a, q, f); break;
-        case 3: hipLaunchKernelGGL(xstage_f32_kernel<3>, grid, block, 0, st, a, q, f); break;
-        case 4: hipLaunchKernelGGL(xstage_f32_kernel<4>, grid, block, 0, st, a, q, f); break;
-        case 5: hipLaunchKernelGGL(xstage_f32_kernel<5>, grid, block, 0, st, a, q, f); break;
-        case 6: hipLaunchKernelGGL(xstage_f32_kernel<6>, grid, block, 0, st, a, q, f); break;
-        case 7: hipLaunchKernelGGL(xstage_f32_kernel<7>, grid, block, 0, st, a, q, f); break;
-        case 8: hipLaunchKernelGGL(xstage_f32_kernel<8>, grid, block, 0, st, a, q, f); break;
-        case 9: hipLaunchKernelGGL(xstage_f32_kernel<9>, grid, block, 0, st, a, q, f); break;
+        case 1: hipLaunchKernelGGL(xstage_f32_kernel<1>, grid, block, q.lds_b, st, a, q, f); break;
+        case 2: hipLaunchKernelGGL(xstage_f32_kernel<2>, grid, block, q.lds_b, st, a, q, f); break;
+        case 3: hipLaunchKernelGGL(xstage_f32_kernel<3>, grid, block, q.lds_b, st, a, q, f); break;
+        case 4: hipLaunchKernelGGL(xstage_f32_kernel<4>, grid, block, q.lds_b, st, a, q, f); break;
+        case 5: hipLaunchKernelGGL(xstage_f32_kernel<5>, grid, block, q.lds_b, st, a, q, f); break;
+        case 6: hipLaunchKernelGGL(xstage_f32_kernel<6>, grid, block, q.lds_b, st, a, q, f); break;
+        case 7: hipLaunchKernelGGL(xstage_f32_kernel<7>, grid, block, q.lds_b, st, a, q, f); break;
+        case 8: hipLaunchKernelGGL(xstage_f32_kernel<8>, grid, block, q.lds_b, st, a, q, f); break;
+        case 9: hipLaunchKernelGGL(xstage_f32_kernel<9>, grid, block, q.lds_b, st, a, q, f); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

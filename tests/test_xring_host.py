@@ -1,5 +1,5 @@
 """The X stage's LDS ring on the host, for every number of inputs, form and work split: the plan fits its
-LDS, gives every wave k-steps to do, and no stage is read before all its transfers have landed or
+LDS, takes no more of it than the block needs, gives every wave k-steps to do, and no stage is read before all its transfers have landed or
 overwritten before it has been read.
 
 The replay runs the kernel's loop (csrc/xring.h holds its plan and its counts) with each wave's
@@ -34,7 +34,12 @@ static void replay(const char* form, int M, int waves, int n_c, const XRing& q, 
     CHECK(q.nch * steps % parts == 0, "%s M=%d waves=%d: %d k-steps per stage for %d waves", form, M, waves, q.nch * steps, parts);
     CHECK(q.chunk_b == (M + 3) / 4 * 4 * kRowB && q.ipw * waves >= q.nch * q.n_inst, "%s M=%d waves=%d: transfers", form, M, waves);
     if (q.nch < 1 || q.depth < 1) return;
-    const int n_stage = ring_stages(q);
+    const int n_stage = q.n_stage;
+    CHECK(n_stage == (q.n_chunk + q.nch - 1) / q.nch && q.n_full == q.n_chunk / q.nch, "%s M=%d n_c=%d: stages", form, M, n_c);
+    CHECK((long)ring_slots(q) * q.chunk_b + behind <= q.lds_b && q.lds_b <= lds_b, "%s M=%d n_c=%d: LDS", form, M, n_c);
+    for (int s = 0; s < n_stage; ++s)                           // the last byte of every stage's chunks
+        CHECK((s % q.depth * q.nch + (s + 1 < n_stage ? q.nch : q.n_chunk - s * q.nch)) * q.chunk_b + behind <= q.lds_b,
+              "%s M=%d n_c=%d: stage %d past the LDS", form, M, n_c, s);
     std::vector<Queue> wave(waves);
     std::vector<int> slot(q.depth, -1), need(n_stage, 0);       // stage held by a slot; its transfers
     auto issue = [&](int s) {
@@ -83,16 +88,19 @@ int main() {
                     const XRing q = ks_ring(i8 != 0, nb, nwv, M, n_c);
                     // where a chunk lacks some of the last row block's rows, a row of zeros sits behind the ring
                     const int behind = (M + 3) / 4 * 4 < 16 * nb ? kRowB : 0, parts = nwv / ks_groups(i8 != 0, nb, nwv);
-                    CHECK(ks_zero_b(nb, M) == behind && ks_parts(i8 != 0, nb, nwv) == parts, "M=%d: split", M);
-                    CHECK(ring_ok(q, ks_steps(i8 != 0), parts), "M=%d waves=%d: the launch refuses its plan", M, nwv);
-                    replay(i8 ? "int8" : "fp16", M, nwv, n_c, q, ks_steps(i8 != 0), parts, ks_lds(nb, nwv), behind);
+                    CHECK(ks_zero_b(nb, M) == behind && (q.parts == parts || (q.parts == 1 && q.n_chunk == 1)), "M=%d: split", M);
+                    CHECK(ring_ok(q, ks_steps(i8 != 0)), "M=%d waves=%d: the launch refuses its plan", M, nwv);
+                    // a block of one chunk leaves room for several workgroups per CU
+                    if (nwv == 4 && nb <= 4 && n_c <= 32) CHECK(q.lds_b <= 163840 / 4, "M=%d n_c=%d: %d B of LDS", M, n_c, q.lds_b);
+                    replay(i8 ? "int8" : "fp16", M, nwv, n_c, q, ks_steps(i8 != 0), parts, ks_lds(i8 != 0, nb, nwv), behind);
                 }
         for (int M = 2; M <= 256; M += 2)
             for (long n_chan : {1L, 64L, 128L, 256L, 257L, 320L, 4096L}) {
-                const XF32 f = f32_split(M, n_chan, 256);
+                const XF32 f = f32_split(M, n_c, n_chan, 256);
                 CHECK(f.tpw >= 1 && f.tpw <= kF32MaxTpw && f.groups * f.n_tg * f.tpw >= f.n_tiles, "fp32 M=%d: split", M);
                 if (f.n_tg < 1) continue;
-                CHECK(ring_ok(f32_ring(f, M, n_c), kF32Steps, kF32Waves / f.n_tg), "fp32 M=%d: the launch refuses its plan", M);
+                CHECK(ring_ok(f32_ring(f, M, n_c), kF32Steps), "fp32 M=%d: the launch refuses its plan", M);
+                if (M <= 64 && n_c <= 32) CHECK(f32_ring(f, M, n_c).lds_b <= 163840 / 4, "fp32 M=%d n_c=%d: LDS", M, n_c);
                 // the last row block's fragments run past the last chunk
                 replay("fp32", M, kF32Waves, n_c, f32_ring(f, M, n_c), kF32Steps, kF32Waves / f.n_tg, kF32LdsB,
                        (16 * f.nb - (M + 3) / 4 * 4) * kRowB);
