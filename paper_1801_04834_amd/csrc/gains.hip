@@ -22,23 +22,26 @@ __device__ __forceinline__ float2 cmul(float2 x, float2 y) {
 }
 __device__ __forceinline__ float2 cconj(float2 x) { return make_float2(x.x, -x.y); }
 
-// Two neighbouring entries (one station pair and p1) per thread: 16-byte loads and stores, no 64-bit
-// division (48 stations, 1024 channels: 17.2 -> 13.3 us; 76 stations: 40 -> 30).
+// Two neighbouring entries (one station pair and p1) per thread: 16-byte loads and stores, one 32-bit
+// division (48 stations, 1024 channels: 17.2 -> 13.3 us; 76 stations: 40 -> 30).  The threads run
+// through the entries of all channels: with whole workgroups per channel a few stations leave most
+// of their threads idle (one station, 131072 channels: 34 us against 7).
 __global__ __launch_bounds__(256) void apply_gains_kernel(const float4* __restrict__ vis0, const float2* __restrict__ gains,
-                                                          float4* __restrict__ vis, int B, int M, int per_ch) {
-    const int64_t ch = blockIdx.x / per_ch;
-    const int e = (int)(blockIdx.x % per_ch) * 256 + threadIdx.x;      // baseline * 2 + p1
-    if (e >= 2 * B) return;
+                                                          float4* __restrict__ vis, unsigned per_ch, int M, unsigned n) {
+    const unsigned id = blockIdx.x * 256u + threadIdx.x;
+    if (id >= n) return;
+    const unsigned ch = id / per_ch;
+    const int e = (int)(id - ch * per_ch);         // baseline * 2 + p1
     const int bl = e >> 1, p1 = e & 1;
     int s1 = (int)((sqrtf(8.f * bl + 1.f) - 1.f) * 0.5f);
     while (s1 * (s1 + 1) / 2 > bl) --s1;
     while ((s1 + 1) * (s1 + 2) / 2 <= bl) ++s1;
     const int s2 = bl - s1 * (s1 + 1) / 2;
-    const float2* g = gains + ch * M;
+    const float2* g = gains + (int64_t)ch * M;
     const float2 ga = g[2 * s1 + p1], g0 = g[2 * s2], g1 = g[2 * s2 + 1];
-    const float4 v = vis0[ch * 2 * B + e];
+    const float4 v = vis0[id];
     const float2 x = cmul(cmul(ga, cconj(g0)), make_float2(v.x, v.y)), y = cmul(cmul(ga, cconj(g1)), make_float2(v.z, v.w));
-    vis[ch * 2 * B + e] = make_float4(x.x, x.y, y.x, y.y);
+    vis[id] = make_float4(x.x, x.y, y.x, y.y);
 }
 
 // v of this lane plus those of all lanes of the wave with the same lane bit 1
@@ -55,11 +58,14 @@ __device__ __forceinline__ float add_same_p1(float v) {
 // One workgroup of >= 4 S threads per channel: thread j = 4 s2 + q, q = 2 p1 + p2 (the entries of a
 // row s1 are 4 (s1 + 1) consecutive ones).  48 stations, 1024 channels: 37.4 us with one thread per
 // input walking its row and its column, 19.2 us in this form (77 MB read: 12.5 us at the copy rate).
-__global__ __launch_bounds__(512) void apply_gains_adjoint_kernel(const float2* __restrict__ vis0, const float2* __restrict__ gains,
+// LDS for up to 16 NW stations, so that small arrays have as many channels in flight as a CU holds
+// waves (one station, 131072 channels: 89 us with LDS for 128 stations, 37 so; 42 with one thread per input).
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void apply_gains_adjoint_kernel(const float2* __restrict__ vis0, const float2* __restrict__ gains,
                                                                   const float2* __restrict__ grad_vis, float2* __restrict__ grad_gains,
                                                                   int S) {
-    __shared__ float2 part[kMaxStations][8][2];    // row sums [s1][wave][p1]
-    __shared__ float2 col[4 * kMaxStations];       // column sums [thread]
+    __shared__ float2 part[16 * NW][NW][2];        // row sums [s1][wave][p1]
+    __shared__ float2 col[64 * NW];                // column sums [thread]
     const int j = threadIdx.x, wave = j >> 6, n_wave = blockDim.x >> 6;
     const int s2 = j >> 2, p1 = (j >> 1) & 1, p2 = j & 1;
     const int64_t ch = blockIdx.x;
@@ -113,15 +119,14 @@ __global__ __launch_bounds__(512) void apply_gains_adjoint_kernel(const float2* 
 }  // namespace
 
 hipError_t launch_apply_gains(const void* vis0, const void* gains, void* vis, int n_chan, int S, hipStream_t st) {
-    const int B = S * (S + 1) / 2, per_ch = (2 * B + 255) / 256;
-    // whole workgroups per channel: with few stations and millions of channels in pieces, since a
-    // launch holds fewer than 2^32 work-items
-    const int piece = (1 << 22) / per_ch;
+    const int per_ch = S * (S + 1);                // entry pairs of a channel
+    // millions of channels in pieces: a launch holds fewer than 2^32 work-items
+    const int piece = (1 << 30) / per_ch;
     hipError_t e = hipSuccess;
     for (int64_t c0 = 0; c0 < n_chan && e == hipSuccess; c0 += piece) {
-        const int64_t n = n_chan - c0 < piece ? n_chan - c0 : piece;
-        hipLaunchKernelGGL(apply_gains_kernel, dim3((unsigned)(n * per_ch)), dim3(256), 0, st, (const float4*)vis0 + c0 * 2 * B,
-                           (const float2*)gains + c0 * 2 * S, (float4*)vis + c0 * 2 * B, B, 2 * S, per_ch);
+        const unsigned n = (unsigned)((n_chan - c0 < piece ? n_chan - c0 : piece) * per_ch);
+        hipLaunchKernelGGL(apply_gains_kernel, dim3((n + 255) / 256), dim3(256), 0, st, (const float4*)vis0 + c0 * per_ch,
+                           (const float2*)gains + c0 * 2 * S, (float4*)vis + c0 * per_ch, (unsigned)per_ch, 2 * S, n);
         e = hipGetLastError();
     }
     return e;
@@ -130,8 +135,14 @@ hipError_t launch_apply_gains(const void* vis0, const void* gains, void* vis, in
 hipError_t launch_apply_gains_adjoint(const void* vis0, const void* gains, const void* grad_vis, void* grad_gains, int n_chan,
                                       int S, hipStream_t st) {
     if (n_chan == 0) return hipSuccess;
-    hipLaunchKernelGGL(apply_gains_adjoint_kernel, dim3((unsigned)n_chan), dim3((unsigned)((4 * S + 63) / 64 * 64)), 0, st,
-                       (const float2*)vis0, (const float2*)gains, (const float2*)grad_vis, (float2*)grad_gains, S);
+    const dim3 grid((unsigned)n_chan), block((unsigned)((4 * S + 63) / 64 * 64));
+    const float2 *v = (const float2*)vis0, *g = (const float2*)gains, *G = (const float2*)grad_vis;
+    float2* out = (float2*)grad_gains;
+    if (S <= 16) hipLaunchKernelGGL(apply_gains_adjoint_kernel<1>, grid, block, 0, st, v, g, G, out, S);
+    else if (S <= 32) hipLaunchKernelGGL(apply_gains_adjoint_kernel<2>, grid, block, 0, st, v, g, G, out, S);
+    else if (S <= 64) hipLaunchKernelGGL(apply_gains_adjoint_kernel<4>, grid, block, 0, st, v, g, G, out, S);
+    else if (S <= kMaxStations) hipLaunchKernelGGL(apply_gains_adjoint_kernel<8>, grid, block, 0, st, v, g, G, out, S);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
