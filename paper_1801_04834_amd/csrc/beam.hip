@@ -397,61 +397,71 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(beam_wa
 //    waves, 157 with two, 117 with one; 13 stations, 40 beams, IQUV: 102 / 87 / 136; 48 stations,
 //    32 beams: 168 / 191 / 224), two up to 24 stations for Stokes I.
 //  - Few channels leave CUs idle or a long last round: below two rounds of resident workgroups the
-//    channel's time is split into parts of whole windows and at least four blocks, as many as give
-//    the least rounds per part; each part repeats the weights (about 4 % of a part).  30 stations,
-//    128 channels of 3072 samples: 215 us in one part, 112 in two, 64 in four; 48 stations, 1024
-//    channels: 160 / 143 / 150; 24 stations, 1536 channels of 7 blocks: 38 / 39 / 47.
+//    channel's time is split into parts of whole windows and at least four blocks.  The fullest CU
+//    runs its workgroups `occ` at a time (asked of the runtime: registers and LDS hold three to
+//    sixteen), and k of them take the time of one up to `sat`, k / sat beyond: one and two waves
+//    with Stokes I are bound by the channel's stream from about 48 KB of blocks in flight on a CU
+//    (12 / KS workgroups), the others by their own products as far as the CU holds them.  Each part
+//    repeats the weights (about 4 % of a part).  us in 1 / 2 / 3 / 4 / 6 parts, blocks of 96 x 32 samples unless said:
+//      30 stations, 128 channels 215 / 112 / - / 64;  48 stations, 1024 channels 160 / 143 / 150
+//      2 stations, 1 beam, I (one wave, 16 resident): 1024 channels 89 / 61 / 54 / 52 / 54
+//      13 stations, 1 beam, I (two waves, 8 resident): 512 channels 129 / 71 / 66 / 61 / 72;
+//        1024 130 / 127 / 148 / 143 / 137;  1536 193 / 224 / 215 / 206 / 197
+//      20 stations, 1 beam, I (two waves, 6 resident): 256 channels 128 / 70 / 53 / 44 / 44;
+//        512 158 / 95 / 99 / 117 / 111;  1024 186 / 231 / 218 / 202 / 204;  1536 290 / 325 / 309 / 303 / 295;
+//        2048 of 24 blocks 118 / 106 / 109 / 112 / 124
+//      20 stations, 20 beams, IQUV (four waves, 4 resident): 512 347 / 228 / 281 / 246 / 245;
+//        1024 448 / 480 / 482 / 481 / 482;  1536 826 / 710 / 711 / 711 / 705
 template <int KS, int NS>
 int beam_nw(int tiles) {
     if (KS == 1 && tiles == 1) return 1;
     return tiles <= 2 && (KS <= 2 || (KS == 3 && NS == 1)) ? 2 : 4;
 }
-int beam_kb_part(const BeamArgs& a, int64_t groups, int resident) {
+int beam_kb_part(const BeamArgs& a, int64_t groups, int occ, int sat) {
     const int unit = a.n_int > kBT ? a.n_int / kBT : 1;                 // blocks of a window
     int best = (a.n_kb + unit - 1) / unit * unit;                       // one part
-    if (groups >= 2 * resident) return best;
+    if (groups >= 2 * occ * kCUs) return best;
+    const auto together = [&](int64_t k) { return k > sat ? (double)k / sat : k > 0 ? 1.0 : 0.0; };
     double least = 1e30;
     for (int parts = 1; parts <= 16; ++parts) {
         const int per = ((a.n_kb + parts - 1) / parts + unit - 1) / unit * unit;
         if (parts > 1 && per < 4) break;
-        const int64_t n = (a.n_kb + per - 1) / per;
-        const double t = (double)((groups * n + resident - 1) / resident) * per * (1.0 + 0.04 * (double)(n - 1));
+        const int64_t n = (a.n_kb + per - 1) / per, load = (groups * n + kCUs - 1) / kCUs;
+        const double t = ((double)(load / occ) * together(occ) + together(load % occ)) * per * (1.0 + 0.04 * (double)(n - 1));
         if (t < least) { least = t; best = per; }
     }
     return best;
 }
 
+template <int KS, int NS, bool VOLT, int NW>
+hipError_t launch_nw(BeamArgs a, int gy, hipStream_t st) {
+    static const int per_cu = [] {
+        int n = 0;
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, beam_kernel<KS, NS, VOLT, NW>, 64 * NW, 0);
+        return e == hipSuccess && n > 0 ? n : 4 * beam_waves<KS>() / NW;
+    }();
+    a.kb_part = beam_kb_part(a, (int64_t)a.n_chan * gy, per_cu, NW < 4 && NS == 1 && 12 / KS < per_cu ? 12 / KS : per_cu);
+    const dim3 grid((unsigned)a.n_chan, (unsigned)gy, (unsigned)((a.n_kb + a.kb_part - 1) / a.kb_part));
+    hipLaunchKernelGGL((beam_kernel<KS, NS, VOLT, NW>), grid, dim3(64 * NW), 0, st, a);
+    return hipGetLastError();
+}
 // VOLT: the voltage output is compiled in only where voltages are asked for
 template <int KS, int NS, bool VOLT>
-void launch_vs(BeamArgs a, hipStream_t st) {
+hipError_t launch_vs(const BeamArgs& a, hipStream_t st) {
     const int tiles = (a.NB + 31) / 32, nw = beam_nw<KS, NS>(tiles), gy = (tiles + nw - 1) / nw;
-    a.kb_part = beam_kb_part(a, (int64_t)a.n_chan * gy, kCUs * 4 * beam_waves<KS>() / nw);
-    const dim3 grid((unsigned)a.n_chan, (unsigned)gy, (unsigned)((a.n_kb + a.kb_part - 1) / a.kb_part)), block(64 * nw);
     if constexpr (KS == 1) {
-        if (nw == 1) {
-            hipLaunchKernelGGL((beam_kernel<KS, NS, VOLT, 1>), grid, block, 0, st, a);
-            return;
-        }
+        if (nw == 1) return launch_nw<KS, NS, VOLT, 1>(a, gy, st);
     }
     if constexpr (KS <= 2 || (KS == 3 && NS == 1)) {
-        if (nw == 2) {
-            hipLaunchKernelGGL((beam_kernel<KS, NS, VOLT, 2>), grid, block, 0, st, a);
-            return;
-        }
+        if (nw == 2) return launch_nw<KS, NS, VOLT, 2>(a, gy, st);
     }
-    hipLaunchKernelGGL((beam_kernel<KS, NS, VOLT, 4>), grid, block, 0, st, a);
+    return launch_nw<KS, NS, VOLT, 4>(a, gy, st);
 }
 template <int KS>
 hipError_t launch_ks(const BeamArgs& a, hipStream_t st) {
     const bool v = a.voltages != nullptr;
-    if (a.n_stokes == 1) {
-        if (v) launch_vs<KS, 1, true>(a, st);
-        else launch_vs<KS, 1, false>(a, st);
-    } else {
-        if (v) launch_vs<KS, 4, true>(a, st);
-        else launch_vs<KS, 4, false>(a, st);
-    }
-    return hipGetLastError();
+    if (a.n_stokes == 1) return v ? launch_vs<KS, 1, true>(a, st) : launch_vs<KS, 1, false>(a, st);
+    return v ? launch_vs<KS, 4, true>(a, st) : launch_vs<KS, 4, false>(a, st);
 }
 
 }  // namespace
