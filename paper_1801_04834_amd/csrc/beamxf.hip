@@ -388,14 +388,16 @@ __global__ __launch_bounds__(kXThreads, 4) void beam_transform_kernel(TfArgs a) 
     }
 }
 
-// Windows of two n1 or more for Stokes I; of four or more for IQUV, whose sums over the polarisations
-// at each window's end cost more than they save in windows of two (20 beams, c_out 4, n_int 8: 16.9 us
-// against 19.3 us; c_out 2, n_int 16: 17.0 against 18.8).
+// Windows of two n1 or more for Stokes I; for IQUV, whose sums over the polarisations at each window's
+// end cost more than they save in short windows, of four n1 and 32 samples or more (20 beams, c_out 4,
+// n_int 8: 16.9 us against 19.3 us; c_out 2, n_int 16: 17.0 against 18.8; 4 subbands, 300 channel
+// samples, 33 beams: 8 / 8 58.4 against 63.5, 4 / 16 55.3 against 58.6, but 4 / 32 63.3 against 54.9 and
+// 8 / 32 63.2 against 54.2).
 template <int COUT, int NS>
 void launch_stokes(const TfArgs& a, hipStream_t st) {
     const dim3 grid((unsigned)((int64_t)a.SB * a.n_c)), block(kXThreads);
     if constexpr (COUT < 16) {
-        if (a.n_int >= (NS == 1 ? 2 : 4) * (16 / COUT)) {
+        if (a.n_int >= (NS == 1 ? 2 : 4) * (16 / COUT) && (NS == 1 || a.n_int >= 32)) {
             hipLaunchKernelGGL((beam_transform_kernel<COUT, NS, true>), grid, block, 0, st, a);
             return;
         }
