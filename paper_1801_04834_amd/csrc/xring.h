@@ -68,6 +68,14 @@ constexpr bool ring_ok(const XRing& q, int steps) {
 // ---- FP16-split and int8: nwv waves per channel, nb row blocks of 16 ----
 constexpr int ks_kc(bool int8) { return int8 ? 128 : 32; }         // channel samples per chunk
 constexpr int ks_steps(bool int8) { return int8 ? 4 : 2; }         // k-steps per chunk (of 32 / 16 samples)
+// Blocks of one chunk at up to 2 row blocks take one wave per channel (its few products are done before
+// several waves could have added theirs up, and a CU holds up to 32 channels: 16384 channels, us with four
+// waves and one: FP16-split 32 samples, 1 station 39 and 9, 12 stations 55 and 26; int8 128 samples, 1
+// station 37 and 9, 12 stations 51 and 24; 16 stations FP16-split 47 and 35).  At most one channel per CU
+// takes eight waves, the rest four.
+constexpr int ks_waves(bool int8, int nb, int n_c, long n_chan, int cus) {
+    return nb <= 2 && n_c <= ks_kc(int8) ? 1 : n_chan <= cus ? 8 : 4;
+}
 constexpr int ks_groups(bool int8, int nb, int nwv) {
     if (nb <= 3) return 1;
     if (nb <= 5) return nwv == 8 ? 2 : 1;
@@ -104,8 +112,7 @@ constexpr XRing ks_ring(bool int8, int nb, int nwv, int M, int n_c) {
     // subbands 42.6 us, with two chunks per stage 38.4)
     if (int8 && nb == 2 && nwv == 4) mult = 2;
     XRing q = make_ring(ks_kc(int8), M, n_c, nwv, ks_lds(int8, nb, nwv) - ks_zero_b(nb, M), mult);
-    // one chunk and up to three tiles: their sums over the waves would take longer than the products
-    q.parts = nb <= 2 && q.n_chunk <= 1 ? 1 : parts;
+    q.parts = parts;
     const int ring = ring_slots(q) * q.chunk_b + ks_zero_b(nb, M), sums = ks_sums(int8, nb, nwv);
     q.lds_b = nb > 8 ? ks_lds(int8, nb, nwv) : ring > sums ? ring : sums;
     return q;

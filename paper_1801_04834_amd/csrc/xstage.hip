@@ -134,19 +134,23 @@ __device__ __forceinline__ void ring_issue(const XArgs& a, const XRing& q, const
     }
 }
 
-// Zero columns >= n_c of the last chunk (`cols` of them from its column `first`) for rows < M.
+// Zero columns >= n_c of the last chunk, of which `first` > 0 are kept, for rows < M: whole granules, the
+// granule that holds both kinds by mask (its samples have landed).
 template <int MODE>
-__device__ __forceinline__ void zero_columns(const XArgs& a, char* buf, int first, int cols, int tid, int nthr) {
-    for (int id = tid; id < a.M * cols; id += nthr) {
-        const int row = id / cols, c = first + id % cols;
-        if constexpr (MODE == XM_FP32) {
-            *(uint2*)(buf + lds_off(row, c >> 1) + (c & 1) * 8) = make_uint2(0u, 0u);
-        } else if constexpr (MODE == XM_FP16_SPLIT) {
-            *(unsigned*)(buf + lds_off(row, c >> 2) + (c & 3) * 4) = 0u;        // hi
-            *(unsigned*)(buf + lds_off(row, 8 + (c >> 2)) + (c & 3) * 4) = 0u;  // lo
-        } else {
-            *(unsigned short*)(buf + lds_off(row, c >> 3) + (c & 7) * 2) = 0;
+__device__ __forceinline__ void zero_columns(const XArgs& a, char* buf, int first, int tid, int nthr) {
+    constexpr int kPer = MODE == XM_FP32 ? 2 : MODE == XM_FP16_SPLIT ? 4 : 8;   // samples per granule
+    constexpr int kPlane = MODE == XM_FP16_SPLIT ? 8 : 16;                      // granules of a row and plane
+    const int g0 = first / kPer, keep = first % kPer * (16 / kPer);   // bytes kept of granule g0
+    const int n = kPlane - g0;
+    for (int id = tid; id < a.M * n; id += nthr) {
+        const int row = id / n, g = g0 + id % n;
+        uintx4 mask = {};
+        if (g == g0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) mask[e] = keep >= 4 * e + 4 ? 0xffffffffu : keep > 4 * e ? 0xffffu : 0u;
         }
+#pragma unroll
+        for (int p = 0; p < 16; p += kPlane) *(uintx4*)(buf + lds_off(row, p + g)) &= mask;
     }
 }
 
@@ -168,8 +172,7 @@ __device__ __forceinline__ void ring_loop(const XArgs& a, const XRing& q, const 
         if (++slot == q.depth) slot = 0;
         const int nch = min(q.nch, q.n_chunk - s * q.nch);
         if (s == q.n_stage - 1 && a.n_c % kc != 0) {
-            const int first = a.n_c % kc;
-            zero_columns<MODE>(a, buf + (nch - 1) * q.chunk_b, first, kc - first, tid, 64 * NWV);
+            zero_columns<MODE>(a, buf + (nch - 1) * q.chunk_b, a.n_c % kc, tid, 64 * NWV);
             lds_barrier();
         }
         body(buf, nch);
@@ -186,12 +189,12 @@ __device__ __forceinline__ void ring_loop(const XArgs& a, const XRing& q, const 
 // needed costs time also where no pipe is full.  Hence tiles of 16 (48 inputs: 30 MFMAs of 16x16x32
 // per 16 samples against 28 of twice the length with tiles of 32), zeros for the padding rows and
 // two instead of three products on the diagonal.  Four waves per workgroup and two or more
-// workgroups per CU; with at most one channel per CU eight waves and the whole LDS as ring.
-// Groups are as few as the accumulators and fragments allow without spilling.
+// workgroups per CU; with at most one channel per CU eight waves and the whole LDS as ring; one wave for
+// the shortest blocks of small arrays.  Groups are as few as the accumulators and fragments allow without spilling.
 // Measured against one workgroup of four waves with up to four 32 x 32 tiles each (waves idle below
 // 5 row blocks of 32), us, FP16-split: 24 st x 32 SB 604 -> 428 (5.7 TB/s); 48 x 16 640 -> 545;
-// 52 x 61 2905 -> 2240; 76 x 64 4030 -> 3780; 24 x 1 125 -> 49; 48 x 1 at 256 channels 54 -> 36.
-// int8: 24 x 32 143 -> 112; 76 x 64 944 -> 932.
+// 52 x 61 2905 -> 2240; 76 x 64 4030 -> 3780; 24 x 1 125 -> 49; 48 x 1 at 256 channels 54 -> 36;
+// 80 x 32 2094 -> 1972.  int8: 24 x 32 118 -> 108; 28 x 32 128 -> 125; 76 x 64 910 -> 884.
 template <int MODE, int NB, int NWV> constexpr int ks_per() {
     return (tile_count(NB) + ks_groups(MODE == XM_INT8, NB, NWV) - 1) / ks_groups(MODE == XM_INT8, NB, NWV);
 }
@@ -199,7 +202,7 @@ template <int MODE, int NB, int NWV, int G> constexpr int ks_tiles() {
     const int left = tile_count(NB) - G * ks_per<MODE, NB, NWV>();
     return left < ks_per<MODE, NB, NWV>() ? left : ks_per<MODE, NB, NWV>();
 }
-template <int NB, int NWV> constexpr int ks_waves_per_simd() { return NWV == 8 ? 2 : NB <= 2 ? 4 : NB == 3 ? 3 : 2; }
+template <int NB, int NWV> constexpr int ks_waves_per_simd() { return NWV == 8 ? 2 : NWV == 1 || NB <= 2 ? 4 : NB == 3 ? 3 : 2; }
 // row blocks used by tiles [t0, t0 + n)
 constexpr unsigned ks_blocks(int NB, int t0, int n) {
     unsigned m = 0;
@@ -263,7 +266,6 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
     constexpr int kTG = ks_groups(MODE == XM_INT8, NB, NWV), kPer = ks_per<MODE, NB, NWV>(), T0 = G * kPer, NT = ks_tiles<MODE, NB, NWV, G>(), kKP = ks_parts(MODE == XM_INT8, NB, NWV);
     constexpr unsigned kUsed = ks_blocks(NB, T0, NT);
     constexpr bool kSplit = MODE == XM_FP16_SPLIT;
-    constexpr bool kOne = NB <= 2;                                      // the waves of part 0 may do all k-steps
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, kpart = wave / kTG;
     const int row = lane & 15, kg = lane >> 4;
 
@@ -286,7 +288,7 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
     }
 
     ring_loop<MODE, NWV>(a, q, chan, lds, tid, [&](char* buf, int nch) {
-        for (int id = kOne && kpart >= q.parts ? nch * kSteps : kpart; id < nch * kSteps; id += kOne ? q.parts : kKP) {
+        for (int id = kpart; id < nch * kSteps; id += kKP) {
             const char* base = buf + (id / kSteps) * q.chunk_b + row * kRowB + (((4 * (id % kSteps) + kg) ^ row) << 4);
             const char* last = pad ? zeros : base + 16 * (NB - 1) * kRowB;
             if constexpr (MODE == XM_FP16_SPLIT) {
@@ -355,15 +357,14 @@ __device__ __forceinline__ void xks_wave(const XArgs& a, const XRing& q, const c
     constexpr int kStride = kTG * ((kPer + 1) / 2) * 2 * 64;            // accumulators between k parts' areas
     static_assert(kKP == 1 || kKP * kStride * 16 <= ks_sums(MODE == XM_INT8, NB, NWV), "partial sums inside LDS");
     int t_own = T0, n_own = NT;
-    if (kOne && q.parts == 1) n_own = kpart == 0 ? NT : 0;
-    else ks_reduce<kPer, kKP>(re, im, (acc_t*)lds + kpart * kStride + G * (kStride / kTG), kpart, kStride, lane, t_own, n_own);
+    ks_reduce<kPer, kKP>(re, im, (acc_t*)lds + kpart * kStride + G * (kStride / kTG), kpart, kStride, lane, t_own, n_own);
 
     // ---- stored baselines s1 >= s2, all four polarisation products ----
     const int64_t ch = blockIdx.x;
     const int64_t n_bl = (int64_t)a.S * (a.S + 1) / 2;
     float* tr = (float*)lds + wave * (2 * 16 * 17);
 #pragma unroll
-    for (int t = 0; t < (kOne ? kPer : ks_left(kPer, kKP)); ++t) {
+    for (int t = 0; t < ks_left(kPer, kKP); ++t) {
         if (t >= n_own) continue;
         int J = 0, I = t_own + t;                                       // tile t_own + t of the column-major list
         while (I >= NB - J) { I -= NB - J; ++J; }
@@ -434,7 +435,11 @@ hipError_t launch_ksplit(const XArgs& a, hipStream_t st) {
 }
 template <int MODE, int NB>
 hipError_t launch_ksplit(const XArgs& a, hipStream_t st) {
-    return a.n_chan <= kCUs ? launch_ksplit<MODE, NB, 8>(a, st) : launch_ksplit<MODE, NB, 4>(a, st);
+    const int nwv = ks_waves(MODE == XM_INT8, NB, a.n_c, a.n_chan, kCUs);
+    if constexpr (NB <= 2) {
+        if (nwv == 1) return launch_ksplit<MODE, NB, 1>(a, st);
+    }
+    return nwv == 8 ? launch_ksplit<MODE, NB, 8>(a, st) : launch_ksplit<MODE, NB, 4>(a, st);
 }
 
 template <int MODE>

@@ -1,6 +1,6 @@
-"""X stage on blocks of one or two LDS chunks, few and many channels: up to 16 stations one wave does all
-k-steps (FP16-split to 32, int8 to 128 channel samples), in FP32 mode up to 64 samples no wave splits them.
-Against the oracle.
+"""X stage on blocks of one or two LDS chunks, few and many channels: up to 16 stations a channel has one
+wave (FP16-split to 32, int8 to 128 channel samples), in FP32 mode up to 64 samples no wave splits the
+k-steps.  Against the oracle.
 
 FP32: every sum has at most 128 products per part, coherence error <= 1e-6; FP16-split <= 1e-5, the bound of
 the 16-bit mode; int8: exact integers.  Positions past N_c hold NaN (int8: 99): they must not enter the sums.
