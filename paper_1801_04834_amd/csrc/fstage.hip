@@ -492,10 +492,12 @@ __global__ __launch_bounds__(C) __attribute__((amdgpu_waves_per_eu(fstage_waves<
                 ph = phasor_rev(fma((double)(2 * kW * q), c1, c0));
             } else {
                 // the fused products are spelt out: left to the compiler, their choice moves with the code
-                // around them, and the last bit with it (requantised samples have to stay the same; 16-bit
-                // input at 64 channels has always fused the other product)
+                // around them, and the last bit with it.  Which product of the imaginary part is fused is as
+                // it has always been: with 64 channels the other one in FP16-split output, whatever the
+                // samples' type, and in requantised 16-bit samples (1 value in 2e6 would flip).
+                constexpr bool kOther = C == 64 && (OM == XM_FP16_SPLIT || (OM == XM_INT8 && ST == ST_CI16));
                 const float pr_ = fmaf(step.x, ph.x, -(ph.y * step.y));
-                if constexpr (ST == ST_CI16 && C == 64) ph.y = fmaf(step.y, ph.x, ph.y * step.x);
+                if constexpr (kOther) ph.y = fmaf(step.y, ph.x, ph.y * step.x);
                 else ph.y = fmaf(step.x, ph.y, ph.x * step.y);
                 ph.x = pr_;
             }
