@@ -130,10 +130,7 @@ template <> struct Samp<ST_CI16> {
     }
 };
 template <> struct Samp<ST_CI8> {
-    using raw_t = uint16_t;
-    static __device__ __forceinline__ float2 cvt(raw_t w) {
-        return make_float2((float)(int8_t)(w & 0xffu), (float)(int8_t)(w >> 8));
-    }
+    using raw_t = uint16_t;                 // PassBuf converts packed pairs of rows
 };
 template <> struct Samp<ST_CF32> {
     using raw_t = float2;
