@@ -123,7 +123,7 @@ def write_traffic(fetch_dir, write_dir, bench_json, copy_mib=1024):
         src = next((f for prefix, f in KERNEL_SOURCES if name.startswith(prefix)), None)
         if src is None:
             continue
-        files = [src, "cobalt_internal.h"]
+        files = [src, "cobalt_internal.h"] + (["xring.h"] if src == "xstage.hip" else [])
         if name in mixed:
             out["kernels"][name] = {"sources": files, "source_sha256": source_digest(files),
                                     "mixed_configurations": True}

@@ -392,8 +392,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(beam_wa
 
 // Waves per workgroup (beam tiles of 32 each) and K blocks per workgroup.
 //  - Four waves, so that the staging and the incoherent sums are shared; with few stations a block
-//    is small and these are cheap, and a wave without a beam tile only takes up one of the twelve
-//    places of a CU: one or two waves up to 16 stations (5 stations, 16 beams, us: 203 with four
+//    is small and these are cheap, and a wave without a beam tile only takes up a place on the
+//    CU: one or two waves up to 16 stations (5 stations, 16 beams, us: 203 with four
 //    waves, 157 with two, 117 with one; 13 stations, 40 beams, IQUV: 102 / 87 / 136; 48 stations,
 //    32 beams: 168 / 191 / 224), two up to 24 stations for Stokes I.
 //  - Few channels leave CUs idle or a long last round: below two rounds of resident workgroups the
